@@ -26,7 +26,21 @@ __global__ void __launch_bounds__(512) k_attn(AttnParams p) {
     extern __shared__ float smem[];
     const int m = blockIdx.y;
     if (m >= *p.nrows) return;
-    attn_item<WT, DH, false>(p, m, blockIdx.x, smem);
+    attn_item<WT, DH, false>(p, row_head(p.rows, m), p.rows[m].anc, m, blockIdx.x, smem);
+}
+
+// The same over the rows of a prompt pass: row m is position p0 + m, and every
+// key and value it reads, its own included, is in the committed cache.
+template <typename WT, int DH>
+__global__ void __launch_bounds__(512) k_attn_prompt(AttnParams p, int seq, int p0, int depth) {
+    extern __shared__ float smem[];
+    const int m = blockIdx.y;
+    Row row;
+    row.slot = -1;
+    row.seq = seq;
+    row.pos = row.tdone = p0 + m;
+    row.depth = depth;
+    attn_item<WT, DH, false, true>(p, row, nullptr, m, blockIdx.x, smem);
 }
 
 // Shared-prefix task attention for decode row lists (KV cache management of
@@ -352,13 +366,16 @@ static hipError_t launch_t(const AttnParams& p, int m_cap, float* part, unsigned
 
 template <typename WT>
 static hipError_t allow(int bytes) {
-    const void* f[] = {(const void*)k_attn<WT, 16>, (const void*)k_attn<WT, 32>, (const void*)k_attn<WT, 64>};
+    const void* f[] = {(const void*)k_attn<WT, 16>,        (const void*)k_attn<WT, 32>,
+                       (const void*)k_attn<WT, 64>,        (const void*)k_attn_prompt<WT, 16>,
+                       (const void*)k_attn_prompt<WT, 32>, (const void*)k_attn_prompt<WT, 64>};
     for (const void* x : f) {
         hipError_t e = hipFuncSetAttribute(x, hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
         if (e != hipSuccess) return e;
     }
     if constexpr (sizeof(WT) == 2) {
-        const void* g[] = {(const void*)k_attn<WT, 96>, (const void*)k_attn<WT, 128>};
+        const void* g[] = {(const void*)k_attn<WT, 96>, (const void*)k_attn<WT, 128>,
+                           (const void*)k_attn_prompt<WT, 96>, (const void*)k_attn_prompt<WT, 128>};
         for (const void* x : g) {
             hipError_t e = hipFuncSetAttribute(x, hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
             if (e != hipSuccess) return e;
@@ -370,6 +387,27 @@ static hipError_t allow(int bytes) {
 hipError_t attention_prepare(int lds_bytes) {
     hipError_t e = allow<uint16_t>(lds_bytes);
     return e != hipSuccess ? e : allow<float>(lds_bytes);
+}
+
+template <typename WT, int DH>
+static hipError_t launch_prompt_dh(const AttnParams& p, int seq, int p0, int depth, int M, hipStream_t st) {
+    hipLaunchKernelGGL((k_attn_prompt<WT, DH>), dim3(p.g.H, M), dim3(64 * attention_waves(p.chunks_cap)),
+                       attention_lds_bytes(p.chunks_cap, DH), st, p, seq, p0, depth);
+    return hipGetLastError();
+}
+
+hipError_t launch_attention_prompt(const AttnParams& p, bool bf16, int seq, int p0, int depth, int M, hipStream_t st) {
+    switch (p.g.dh) {
+        case 16: return bf16 ? launch_prompt_dh<uint16_t, 16>(p, seq, p0, depth, M, st)
+                             : launch_prompt_dh<float, 16>(p, seq, p0, depth, M, st);
+        case 32: return bf16 ? launch_prompt_dh<uint16_t, 32>(p, seq, p0, depth, M, st)
+                             : launch_prompt_dh<float, 32>(p, seq, p0, depth, M, st);
+        case 64: return bf16 ? launch_prompt_dh<uint16_t, 64>(p, seq, p0, depth, M, st)
+                             : launch_prompt_dh<float, 64>(p, seq, p0, depth, M, st);
+        case 96: return bf16 ? launch_prompt_dh<uint16_t, 96>(p, seq, p0, depth, M, st) : hipErrorInvalidValue;
+        case 128: return bf16 ? launch_prompt_dh<uint16_t, 128>(p, seq, p0, depth, M, st) : hipErrorInvalidValue;
+    }
+    return hipErrorInvalidValue;
 }
 
 hipError_t launch_attention(const AttnParams& p, bool bf16, int m_cap, float* part, unsigned* cnt, hipStream_t st) {

@@ -4,6 +4,7 @@
 #pragma once
 #include "ls_attn.h"
 #include "ls_gemm_dev.h"   // buffer resources
+#include "ls_prefill.h"    // operand order
 
 namespace ls {
 
@@ -349,7 +350,8 @@ __device__ __forceinline__ void attn_own(const AttnParams& p, const Row& row_in,
     l_out = 1.f;
 }
 
-template <typename WT, int DH, bool COH>
+// OPD: the output goes to p.out in MFMA operand order (prompt rows), else row-major
+template <typename WT, int DH, bool COH, bool OPD = false>
 __device__ __forceinline__ void attn_combine_lds(const AttnParams& p, int m, int head, int n, const float* smem);
 
 // One (row m, head) item by the whole workgroup: its waves take the chunks of
@@ -358,12 +360,11 @@ __device__ __forceinline__ void attn_combine_lds(const AttnParams& p, int m, int
 // partials are combined in LDS in chunk order.  COH: inside the persistent
 // pass (device-scope query, own key / value and output).
 // LDS: [chunks + 1][DH + 2] partials.
-template <typename WT, int DH, bool COH>
-__device__ __forceinline__ void attn_item(const AttnParams& p, int m, int head, float* smem) {
+template <typename WT, int DH, bool COH, bool OPD = false>
+__device__ __forceinline__ void attn_item(const AttnParams& p, const Row& row, const int* anc, int m, int head,
+                                          float* smem) {
     using A = AttnGeo<WT, DH>;
     constexpr int E = A::E;
-    const Row row = row_head(p.rows, m);
-    const int* anc = p.rows[m].anc;
     const int tid = tid_local(), wave = tid >> 6, lane = tid & 63, W = blockDim.x >> 6;
     const int np = (row.pos + kChunk - 1) / kChunk, n = np + 1;
     const int t = kv_table(p.g, p.stack, p.layer, row.depth);
@@ -385,7 +386,7 @@ __device__ __forceinline__ void attn_item(const AttnParams& p, int m, int head, 
         }
     }
     __syncthreads();
-    attn_combine_lds<WT, DH, COH>(p, m, head, n, smem);
+    attn_combine_lds<WT, DH, COH, OPD>(p, m, head, n, smem);
     __syncthreads();
 }
 
@@ -394,7 +395,7 @@ __device__ __forceinline__ void attn_item(const AttnParams& p, int m, int head, 
 // sums its chunk values and the weight sums with them in chunk order
 // (partials in groups of CB: every LDS read of a group is issued before any
 // is used; partials past n read partial 0 and weigh nothing).
-template <typename WT, int DH, bool COH>
+template <typename WT, int DH, bool COH, bool OPD>
 __device__ __forceinline__ void attn_combine_lds(const AttnParams& p, int m, int head, int n, const float* smem) {
     const int tid = tid_local();
     constexpr int CB = 8;
@@ -426,7 +427,7 @@ __device__ __forceinline__ void attn_combine_lds(const AttnParams& p, int m, int
             }
         }
         const float r = o / l;
-        const size_t idx = (size_t)m * p.g.h + head * DH + d;
+        const size_t idx = OPD ? prefill_elem<WT>(m, head * DH + d, p.g.h) : (size_t)m * p.g.h + head * DH + d;
         if (sizeof(WT) == 2)
             st_u16<COH>((uint16_t*)p.out + idx, COH ? h_value(r) : f2h(r));
         else

@@ -23,8 +23,8 @@
 //     loads (nontemporal: streamed once per step) and its A loads at entry and
 //     feeds v_mfma_f32_16x16x32_f16 from registers -- one memory round trip,
 //     no LDS staging; k is split over several workgroups per tile when one
-//     workgroup's waves cannot hold it; larger launches (prefill, 64 rows)
-//     stage A through LDS;
+//     workgroup's waves cannot hold it; larger launches (up to 64
+//     rows) stage A through LDS;
 //   * 16-bit models compute in fp16: weights arrive as bf16 and are packed
 //     into fp16 copies; the activations and key/value caches are fp16;
 //   * epilogues: QKV (RoPE on q and k, K/V written to the KV cache of the

@@ -240,7 +240,7 @@ __global__ void __launch_bounds__(kPassThreads) k_pass(PassParams pp) {
                 for (; m + 1 < M && r >= H * attn_parts(m); ++m) r -= H * attn_parts(m);
                 const int parts = attn_parts(m), head = r / parts, part = r - head * parts;
                 if (parts == 1)
-                    attn_item<WT, DH, true>(a, m, head, (float*)smem);
+                    attn_item<WT, DH, true>(a, row_head(a.rows, m), a.rows[m].anc, m, head, (float*)smem);
                 else
                     attn_item_part<WT, DH>(a, m, head, part, parts, pp.apart, pp.acnt, (float*)smem);
             }

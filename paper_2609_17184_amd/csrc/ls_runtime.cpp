@@ -19,6 +19,7 @@
 #include "ls_attn.h"
 #include "ls_gemm.h"
 #include "ls_pass.h"
+#include "ls_prefill.h"
 #include "ls_sample.h"
 #include "ls_sched.h"
 
@@ -31,7 +32,6 @@ using namespace ls;
 
 namespace {
 
-constexpr int kPrefillRows = 64;
 constexpr size_t kLdsBudget = 80 * 1024;     // preferred GEMM workgroup LDS (two workgroups per CU)
 constexpr size_t kLdsMax = 160 * 1024;       // LDS of one CU: the hard limit of a workgroup
 constexpr size_t kSkWideBytes = 64u << 20;   // weight bytes from which launches of 17..64 rows run stream-K
@@ -119,11 +119,14 @@ struct loopspec_handle {
     void *att = nullptr, *act = nullptr, *kvc = nullptr, *kvs = nullptr;
     int32_t *targ = nullptr;
     int32_t* mode = nullptr;
-    // prefill rows: [R+1 depths][64] + coda copies [R][64] + LM-head row
-    Row *pf_rows = nullptr, *pf_coda = nullptr, *pf_last = nullptr;
+    // prompt passes: rows per pass, pass buffers of the core / prelude rows and of the coda rows
+    int pf_cap = 0;
+    PassBuf pfb{}, pfc{};
+    // staged rows of single-row passes (readouts, measurements) and the prompt's last row
+    Row *pf_rows = nullptr, *pf_last = nullptr;
     int32_t *pf_n = nullptr, *pf_one = nullptr, *pf_jobs = nullptr;
     Sched sch{};
-    int xrow_pf = 0, xrow_coda = 0, xrow_pf_coda = 0;
+    int xrow_pf = 0, xrow_coda = 0, xrow_pf_coda = 0, xrow_last = 0;
 
     // host staging (pinned)
     char* pin = nullptr;
@@ -139,7 +142,7 @@ struct loopspec_handle {
     std::vector<PackedLayer> packed;   // MFMA-order copies (owned, in `folded`)
     const void* head_packed = nullptr;
 
-    // gemm configs: [0] direct path (<= 16 rows), [1] 64-row path
+    // gemm configs: [0] direct path (<= 16 rows), [1] 64-row path (decode with more than 16 slots)
     GemmCfg cfg_qkv[2], cfg_o[2], cfg_gu[2], cfg_down[2], cfg_head[2];
     float* gpart = nullptr;       // split-k partials of the direct path
     unsigned* gcnt = nullptr;     // split-k arrival counters (one per tile, zero between launches)
@@ -326,14 +329,14 @@ hipError_t run_gemm(loopspec_t h, GemmParams p, int epi, const GemmCfg& c, int n
 }
 
 // One launch of kernel `k` (0 QKV, 1 attention, 2 O, 3 gate/up, 4 down) of
-// block `l` of a stack over a row list.  big = prefill-sized row list.
+// block `l` of a stack over a row list.  committed: rows without slots, whose
+// keys and values all are in the committed cache (a prompt's last position).
 hipError_t enqueue_kernel_(loopspec_t h, int k, int stack, int l, const Row* rows, const int32_t* nrows,
-                           int rows_cap, bool big) {
+                           int rows_cap, bool committed) {
     const int nt_max = (rows_cap + 15) / 16;
     const int first = stack == STACK_PRE ? 0 : stack == STACK_CORE ? h->g.Lp : h->g.Lp + h->g.Lb;
     const int hd = h->g.h, F = h->g.F;
     const int b = nt_max > 1 ? 1 : 0;            // direct path (<= 16 rows) or 64-row path
-    (void)big;
     const loopspec_handle::PackedLayer& w = h->packed[first + l];
     hipError_t e = hipSuccess;
     switch (k) {
@@ -363,7 +366,7 @@ hipError_t enqueue_kernel_(loopspec_t h, int k, int stack, int l, const Row* row
             a.layer = l;
             a.chunks_cap = h->chunks_cap;
             a.out = h->att;
-            const bool tasks = !big && h->attn_part;
+            const bool tasks = !committed && h->attn_part;
             return launch_attention(a, h->bf16, rows_cap, tasks ? h->attn_part : nullptr, tasks ? h->attn_cnt : nullptr,
                                     h->st);
         }
@@ -399,9 +402,9 @@ hipError_t enqueue_kernel_(loopspec_t h, int k, int stack, int l, const Row* row
 }
 
 hipError_t enqueue_kernel(loopspec_t h, int k, int stack, int l, const Row* rows, const int32_t* nrows,
-                          int rows_cap, bool big) {
+                          int rows_cap, bool committed) {
     const bool armed = prof_arm(h, stack == STACK_CORE && h->prof_kind == LOOPSPEC_PROF_QKV + k);
-    const hipError_t e = enqueue_kernel_(h, k, stack, l, rows, nrows, rows_cap, big);
+    const hipError_t e = enqueue_kernel_(h, k, stack, l, rows, nrows, rows_cap, committed);
     prof_done(h, armed);
     return e;
 }
@@ -467,10 +470,10 @@ PassParams pass_params(loopspec_t h, int stack, const Row* rows, const int32_t* 
 // One pass of a block stack over a row list (starting from the rows' X): the
 // preparation + persistent pass kernel for decode row lists when it is
 // enabled, else the gather + five launches per block.
-hipError_t enqueue_stack(loopspec_t h, int stack, const Row* rows, const int32_t* nrows, int rows_cap, bool big) {
+hipError_t enqueue_stack(loopspec_t h, int stack, const Row* rows, const int32_t* nrows, int rows_cap) {
     const int n = stack == STACK_PRE ? h->g.Lp : stack == STACK_CORE ? h->g.Lb : h->g.Lc;
     hipError_t e;
-    if (!big && h->pass_on && rows_cap <= kPassRows) {
+    if (h->pass_on && rows_cap <= kPassRows) {
         const PassParams pp = pass_params(h, stack, rows, nrows);
         if ((e = launch_pass_prep(pp, h->bf16, rows_cap, h->st)) != hipSuccess) return e;
         const bool armed = prof_arm(h, stack == STACK_CORE && h->prof_kind == LOOPSPEC_PROF_PASS);
@@ -481,7 +484,7 @@ hipError_t enqueue_stack(loopspec_t h, int stack, const Row* rows, const int32_t
     if ((e = launch_gather(h->g, rows, nrows, rows_cap, h->X, h->pb, h->bf16, h->st)) != hipSuccess) return e;
     for (int l = 0; l < n; ++l)
         for (int k = 0; k < 5; ++k) {
-            e = enqueue_kernel(h, k, stack, l, rows, nrows, rows_cap, big);
+            e = enqueue_kernel(h, k, stack, l, rows, nrows, rows_cap, false);
             if (e != hipSuccess) return e;
         }
     return hipSuccess;
@@ -515,10 +518,10 @@ hipError_t enqueue_finalize(loopspec_t h, const Sched& s, int fin_op, int rows_c
 hipError_t enqueue_step(loopspec_t h) {
     Sched& s = h->sch;
     hipError_t e;
-    if ((e = enqueue_stack(h, STACK_CORE, s.rowsB, s.nB, h->S, false)) != hipSuccess) return e;
+    if ((e = enqueue_stack(h, STACK_CORE, s.rowsB, s.nB, h->S)) != hipSuccess) return e;
     if (h->g.Lc) {
         if ((e = launch_copy_rows(h->g, s.rowsC, s.nC, h->S, h->X, h->st)) != hipSuccess) return e;
-        if ((e = enqueue_stack(h, STACK_CODA, s.rowsC, s.nC, h->S, false)) != hipSuccess) return e;
+        if ((e = enqueue_stack(h, STACK_CODA, s.rowsC, s.nC, h->S)) != hipSuccess) return e;
     }
     if ((e = enqueue_head(h, s.rowsC, s.nC, h->S)) != hipSuccess) return e;
     if ((e = enqueue_finalize(h, s, FIN_STEP, h->S)) != hipSuccess) return e;
@@ -526,7 +529,7 @@ hipError_t enqueue_step(loopspec_t h) {
     if ((e = launch_commit_embed(s, h->kvc, h->kvs, h->wbytes, h->embed, h->bf16, h->X, h->st)) != hipSuccess)
         return e;
     if (h->g.Lp) {
-        if ((e = enqueue_stack(h, STACK_PRE, s.rowsP, s.nP, h->S, false)) != hipSuccess) return e;
+        if ((e = enqueue_stack(h, STACK_PRE, s.rowsP, s.nP, h->S)) != hipSuccess) return e;
     }
     return hipSuccess;
 }
@@ -697,17 +700,26 @@ int loopspec_create(const loopspec_dims* dims, const loopspec_config* cfg, void*
         h->own_stream = true;
     }
     HIPCHK(h, gemm_prepare((int)kLdsMax));
+    HIPCHK(h, prefill_prepare());
     const int S = h->S;
-    const int xrows = S + kPrefillRows + std::max(S, kPrefillRows);
+    // a prompt runs in passes of up to pf_cap positions
+    const int P = h->pf_cap = std::min(kPrefillRowsMax, (d.max_ctx + 63) / 64 * 64);
+    const int xrows = S + P + std::max(S, P) + 1;
     h->xrow_pf = S;
-    h->xrow_coda = S + kPrefillRows;
-    h->xrow_pf_coda = S + kPrefillRows;
-    const int rmax = std::max(S, kPrefillRows);
+    h->xrow_coda = S + P;
+    h->xrow_pf_coda = S + P;
+    h->xrow_last = xrows - 1;
+    const int rmax = std::max(S, P);
     const size_t V = d.vocab, tiles = (V + 15) / 16;
     int r;
     if ((r = dalloc(h, &h->X, (size_t)xrows * g.h))) return r;
     if ((r = dalloc(h, (char**)&h->pb.XB, (size_t)kMaxRows * g.h * h->wbytes))) return r;
     if ((r = dalloc(h, &h->pb.SSQR, (size_t)kMaxRows * g.ssq_tiles))) return r;
+    for (PassBuf* b : {&h->pfb, &h->pfc}) {
+        if (b == &h->pfc && g.Lc < 2) break;              // (the last coda block writes keys and values only)
+        if ((r = dalloc(h, (char**)&b->XB, (size_t)P * g.h * h->wbytes))) return r;
+        if ((r = dalloc(h, &b->SSQR, (size_t)P * g.ssq_tiles))) return r;
+    }
     if ((r = dalloc(h, &h->qbuf, (size_t)rmax * g.h))) return r;
     if ((r = dalloc(h, (char**)&h->att, (size_t)rmax * g.h * h->wbytes))) return r;
     if ((r = dalloc(h, (char**)&h->act, (size_t)rmax * g.F * h->wbytes))) return r;
@@ -728,12 +740,11 @@ int loopspec_create(const loopspec_dims* dims, const loopspec_config* cfg, void*
     if ((r = dalloc(h, (char**)&h->kvs, (size_t)S * g.T * 2 * g.h * h->wbytes))) return r;
     if ((r = dalloc(h, &h->rope, (size_t)d.max_ctx * g.dh))) return r;
     if ((r = dalloc(h, &h->mode, 1))) return r;
-    if ((r = dalloc(h, &h->pf_rows, (size_t)(c.R + 1) * kPrefillRows))) return r;
-    if ((r = dalloc(h, &h->pf_coda, (size_t)(c.R + 1) * kPrefillRows))) return r;
+    if ((r = dalloc(h, &h->pf_rows, (size_t)std::max(c.R + 2, kMaxRows)))) return r;
     if ((r = dalloc(h, &h->pf_last, 1))) return r;
     if ((r = dalloc(h, &h->pf_n, 2))) return r;
     h->pf_one = h->pf_n + 1;
-    if ((r = dalloc(h, &h->pf_jobs, 2 * kPrefillRows))) return r;
+    if ((r = dalloc(h, &h->pf_jobs, 2))) return r;
 
     // scheduler tables
     Sched& s = h->sch;
@@ -813,12 +824,12 @@ int loopspec_create(const loopspec_dims* dims, const loopspec_config* cfg, void*
     }
 
     // launch configurations: the direct path (rows <= 16) and the 64-row path
-    // (decode with more than 16 slots, prefill)
+    // (decode with more than 16 slots)
     {
         size_t part_elems = 0, sk_elems = 0;
         int cnt_n = 0;
         for (int b = 0; b < 2; ++b) {
-            const int nt = b ? (kPrefillRows + 15) / 16 : 1;
+            const int nt = b ? (kMaxRows + 15) / 16 : 1;
             struct K { GemmCfg* c; int tiles, K, nmat, epi; } ks[] = {
                 {&h->cfg_qkv[b], 3 * g.h / 16, g.h, 1, EPI_QKV}, {&h->cfg_o[b], g.h / 16, g.h, 1, EPI_RESID},
                 {&h->cfg_gu[b], g.F / 16, g.h, 2, EPI_SWIGLU}, {&h->cfg_down[b], g.h / 16, g.F, 1, EPI_RESID},
@@ -851,8 +862,8 @@ int loopspec_create(const loopspec_dims* dims, const loopspec_config* cfg, void*
         if ((r = dalloc(h, &h->gcnt, (size_t)std::max(cnt_n, 1)))) return r;
         HIPCHK(h, hipMemsetAsync(h->gcnt, 0, (size_t)std::max(cnt_n, 1) * 4, h->st));
     }
-    // (decode and prefill may slice k differently: prefill only fills the
-    // committed cache, which vanilla and LoopSpec decoding then share)
+    // (decode and prompt passes sum k in different orders: a prompt pass only fills
+    // the committed cache, which vanilla and LoopSpec decoding then share)
 
     // persistent pass: one 8-wave workgroup per CU, all co-resident
     {
@@ -887,7 +898,7 @@ int loopspec_create(const loopspec_dims* dims, const loopspec_config* cfg, void*
         h->pass_grid = G;
     }
 
-    h->pin_bytes = std::max<size_t>((size_t)(c.R + 1) * kPrefillRows * sizeof(Row) * 2 + 4096,
+    h->pin_bytes = std::max<size_t>((size_t)std::max(c.R + 2, kMaxRows) * sizeof(Row) + 4096,
                                     (size_t)d.max_seqs * d.max_ctx * 4 + 4096);
     HIPCHK(h, hipHostMalloc((void**)&h->pin, h->pin_bytes, hipHostMallocDefault));
     HIPCHK(h, hipEventCreate(&h->ev0));
@@ -980,13 +991,114 @@ static int init_seq(loopspec_t h, int seq, int n, const int32_t* tok_dev) {
         return fail(h, LOOPSPEC_EHIP, hipGetErrorString(e));
     if ((e = launch_embed(h->g, s.js, s.njs, 1, h->embed, h->bf16, h->X, h->st)) != hipSuccess)
         return fail(h, LOOPSPEC_EHIP, hipGetErrorString(e));
-    if (h->g.Lp && (e = enqueue_stack(h, STACK_PRE, s.rowsP, s.nP, h->S, false)) != hipSuccess)
+    if (h->g.Lp && (e = enqueue_stack(h, STACK_PRE, s.rowsP, s.nP, h->S)) != hipSuccess)
         return fail(h, LOOPSPEC_EHIP, hipGetErrorString(e));
     h->fresh[seq] = 1;
     // the prompt (prefill) or the forced positions (every depth is a readout)
     std::fill(h->coda_cov[seq].begin(), h->coda_cov[seq].end(), 1);
     return LOOPSPEC_OK;
 }
+
+}  // extern "C"
+
+namespace {
+
+// Parameters of a prompt GEMM over m rows from position p0 of a sequence
+PrefillGemm prompt_gemm(loopspec_t h, int seq, int p0, int m) {
+    PrefillGemm p{};
+    p.g = h->g;
+    p.M = m;
+    p.p0 = p0;
+    p.seq = seq;
+    p.kvc = h->kvc;
+    p.rope = h->rope;
+    p.q = h->qbuf;
+    p.act = h->act;
+    return p;
+}
+
+// Block `l` of a stack over a prompt pass at `depth`: state in xin,
+// pass buffers in; the new state goes to xout and buffers out (ls_prefill.h's orders).
+// kv_only: nothing reads the block's output at these positions, so only its
+// keys and values are computed.
+hipError_t enqueue_prompt_block(loopspec_t h, int stack, int l, int depth, int seq, int p0, int m, const float* xin,
+                                const PassBuf& in, float* xout, const PassBuf& out, bool kv_only) {
+    const int first = stack == STACK_PRE ? 0 : stack == STACK_CORE ? h->g.Lp : h->g.Lp + h->g.Lb;
+    const int hd = h->g.h, F = h->g.F, th = hd / kTile;
+    const loopspec_handle::PackedLayer& w = h->packed[first + l];
+    hipError_t e;
+    PrefillGemm p = prompt_gemm(h, seq, p0, m);
+    p.A = in.XB;
+    p.SSQ = in.SSQR;
+    p.K = hd;
+    p.Wp = w.qkv;
+    p.N_mat = hd;
+    p.tile0 = kv_only ? th : 0;
+    p.tiles = 3 * th - p.tile0;
+    p.table = kv_table(h->g, stack, l, depth);
+    if ((e = launch_prefill_gemm(p, EPI_QKV, h->bf16, h->st)) != hipSuccess || kv_only) return e;
+    AttnParams a{};
+    a.g = h->g;
+    a.q = h->qbuf;
+    a.kvc = h->kvc;
+    a.kvs = h->kvs;
+    a.stack = stack;
+    a.layer = l;
+    a.chunks_cap = h->chunks_cap;
+    a.out = h->att;
+    if ((e = launch_attention_prompt(a, h->bf16, seq, p0, depth, m, h->st)) != hipSuccess) return e;
+    p.A = h->att;
+    p.Wp = w.o;
+    p.tile0 = 0;
+    p.tiles = th;
+    p.Xin = xin;
+    p.Xout = xout;
+    p.XBout = out.XB;
+    p.SSQout = out.SSQR;
+    if ((e = launch_prefill_gemm(p, EPI_RESID, h->bf16, h->st)) != hipSuccess) return e;
+    p.A = out.XB;
+    p.SSQ = out.SSQR;
+    p.Wp = w.gu;
+    p.N_mat = F;
+    p.tiles = F / kTile;
+    if ((e = launch_prefill_gemm(p, EPI_SWIGLU, h->bf16, h->st)) != hipSuccess) return e;
+    p.A = h->act;
+    p.K = F;
+    p.Wp = w.down;
+    p.N_mat = hd;
+    p.tiles = th;
+    p.Xin = xout;
+    return launch_prefill_gemm(p, EPI_RESID, h->bf16, h->st);
+}
+
+// One prompt pass: positions p0 .. p0 + m - 1 of a sequence through the
+// prelude, the core blocks at every depth and the coda blocks at every
+// readout depth (their caches are read by later readouts).  The output of the
+// model's last block (the last core block at depth R, or the last coda block
+// at any depth) is read only for the readout of the prompt's last position:
+// elsewhere that block computes its keys and values alone.
+hipError_t enqueue_prompt(loopspec_t h, int seq, int p0, int m) {
+    const int hd = h->g.h, Lp = h->g.Lp, Lb = h->g.Lb, Lc = h->g.Lc, R = h->c.R;
+    float* x = h->X + (size_t)h->xrow_pf * hd;
+    float* xc = h->X + (size_t)h->xrow_pf_coda * hd;
+    hipError_t e = launch_prefill_embed(h->g, h->sch.Y + (size_t)seq * h->d.max_ctx + p0, m, h->embed, h->bf16, x,
+                                        h->pfb, h->st);
+    for (int l = 0; l < Lp && e == hipSuccess; ++l)
+        e = enqueue_prompt_block(h, STACK_PRE, l, 0, seq, p0, m, x, h->pfb, x, h->pfb, false);
+    for (int r = 1; r <= R; ++r) {
+        for (int l = 0; l < Lb && e == hipSuccess; ++l)
+            e = enqueue_prompt_block(h, STACK_CORE, l, r, seq, p0, m, x, h->pfb, x, h->pfb,
+                                     !Lc && r == R && l == Lb - 1);
+        for (int l = 0; l < Lc && e == hipSuccess; ++l)
+            e = enqueue_prompt_block(h, STACK_CODA, l, r, seq, p0, m, l ? xc : x, l ? h->pfc : h->pfb, xc, h->pfc,
+                                     l == Lc - 1);
+    }
+    return e;
+}
+
+}  // namespace
+
+extern "C" {
 
 int loopspec_prefill(loopspec_t h, int32_t seq, const int32_t* ids, int32_t n, int32_t* first_tok) {
     if (!h) return LOOPSPEC_EINVAL;
@@ -996,77 +1108,46 @@ int loopspec_prefill(loopspec_t h, int32_t seq, const int32_t* ids, int32_t n, i
     if (n + 2 > h->d.max_ctx) return fail(h, LOOPSPEC_ECAPACITY, "prompt does not fit max_ctx");
     for (int i = 0; i < n; ++i)
         if (ids[i] < 0 || ids[i] >= h->d.vocab) return fail(h, LOOPSPEC_EINVAL, "token id out of range");
-    const int R = h->c.R;
-    const int Lc = h->g.Lc;
+    const int Lc = h->g.Lc, P = h->pf_cap;
     Sched& s = h->sch;
-    hipError_t e;
-    int32_t zero = 0;
-    HIPCHK(h, hipMemcpyAsync(s.err, &zero, 4, hipMemcpyHostToDevice, h->st));
-    for (int p0 = 0; p0 < n; p0 += kPrefillRows) {
-        const int m = std::min(kPrefillRows, n - p0);
-        HIPCHK(h, hipStreamSynchronize(h->st));                 // staging buffer is free
-        Row* rows = (Row*)h->pin;
-        Row* coda = rows + (R + 1) * kPrefillRows;
-        int32_t* misc = (int32_t*)(coda + (R + 1) * kPrefillRows);
-        for (int r = 0; r <= R; ++r)
-            for (int i = 0; i < m; ++i) {
-                Row x{};
-                x.xrow = h->xrow_pf + i;
-                x.slot = -1;
-                x.seq = seq;
-                x.pos = p0 + i;
-                x.depth = r;
-                x.tdone = p0 + i;
-                x.src = x.xrow;
-                rows[r * kPrefillRows + i] = x;
-                x.xrow = h->xrow_pf_coda + i;
-                coda[r * kPrefillRows + i] = x;
-            }
-        misc[0] = m;
-        misc[1] = 1;
-        for (int i = 0; i < m; ++i) {
-            misc[2 + 2 * i] = h->xrow_pf + i;
-            misc[3 + 2 * i] = ids[p0 + i];
-        }
-        HIPCHK(h, hipMemcpyAsync(h->pf_rows, rows, sizeof(Row) * (R + 1) * kPrefillRows, hipMemcpyHostToDevice, h->st));
-        HIPCHK(h, hipMemcpyAsync(h->pf_coda, coda, sizeof(Row) * (R + 1) * kPrefillRows, hipMemcpyHostToDevice, h->st));
-        HIPCHK(h, hipMemcpyAsync(h->pf_n, misc, 8, hipMemcpyHostToDevice, h->st));
-        HIPCHK(h, hipMemcpyAsync(h->pf_jobs, misc + 2, 8 * m, hipMemcpyHostToDevice, h->st));
-        if ((e = launch_embed(h->g, h->pf_jobs, h->pf_n, m, h->embed, h->bf16, h->X, h->st)) != hipSuccess)
+    hipError_t e = hipSuccess;
+    // staging: the last position's row, its count, a zero; then the prompt's ids, which
+    // become positions 0..n-1 of the sequence's token record (committed tokens follow them)
+    HIPCHK(h, hipStreamSynchronize(h->st));                     // staging buffer is free
+    Row* last = (Row*)h->pin;
+    int32_t* misc = (int32_t*)(last + 1);
+    int32_t* tok_in = misc + 2;
+    const int m_last = (n - 1) % P + 1;                         // rows of the last pass
+    *last = Row{};
+    last->xrow = h->xrow_last;
+    last->slot = -1;
+    last->seq = seq;
+    last->pos = last->tdone = n - 1;
+    last->depth = h->c.R;
+    last->src = last->xrow;
+    misc[0] = 1;
+    misc[1] = 0;
+    std::memcpy(tok_in, ids, 4 * (size_t)n);
+    HIPCHK(h, hipMemcpyAsync(s.err, misc + 1, 4, hipMemcpyHostToDevice, h->st));
+    HIPCHK(h, hipMemcpyAsync(h->pf_last, last, sizeof(Row), hipMemcpyHostToDevice, h->st));
+    HIPCHK(h, hipMemcpyAsync(h->pf_one, misc, 4, hipMemcpyHostToDevice, h->st));
+    HIPCHK(h, hipMemcpyAsync(s.Y + (size_t)seq * h->d.max_ctx, tok_in, 4 * (size_t)n, hipMemcpyHostToDevice, h->st));
+    for (int p0 = 0; p0 < n; p0 += P)
+        if ((e = enqueue_prompt(h, seq, p0, std::min(P, n - p0))) != hipSuccess)
             return fail(h, LOOPSPEC_EHIP, hipGetErrorString(e));
-        if (h->g.Lp && (e = enqueue_stack(h, STACK_PRE, h->pf_rows, h->pf_n, kPrefillRows, true)) != hipSuccess)
-            return fail(h, LOOPSPEC_EHIP, hipGetErrorString(e));
-        for (int r = 1; r <= R; ++r) {
-            const Row* rr = h->pf_rows + r * kPrefillRows;
-            if ((e = enqueue_stack(h, STACK_CORE, rr, h->pf_n, kPrefillRows, true)) != hipSuccess)
-                return fail(h, LOOPSPEC_EHIP, hipGetErrorString(e));
-            // coda caches of every readout depth (they are read by later readouts)
-            if (Lc) {
-                const Row* cr = h->pf_coda + r * kPrefillRows;
-                if ((e = launch_copy_rows(h->g, cr, h->pf_n, kPrefillRows, h->X, h->st)) != hipSuccess)
-                    return fail(h, LOOPSPEC_EHIP, hipGetErrorString(e));
-                if ((e = enqueue_stack(h, STACK_CODA, cr, h->pf_n, kPrefillRows, true)) != hipSuccess)
-                    return fail(h, LOOPSPEC_EHIP, hipGetErrorString(e));
-            }
-        }
-        if (p0 + m == n) {
-            // readout of the last prompt position at depth R
-            Row last = (Lc ? coda : rows)[R * kPrefillRows + m - 1];
-            HIPCHK(h, hipMemcpyAsync(h->pf_last, &last, sizeof(Row), hipMemcpyHostToDevice, h->st));
-            if ((e = enqueue_head(h, h->pf_last, h->pf_one, 1)) != hipSuccess)
-                return fail(h, LOOPSPEC_EHIP, hipGetErrorString(e));
-            Sched t = s;
-            t.rowsC = h->pf_last;
-            t.nC = h->pf_one;
-            if ((e = enqueue_finalize(h, t, FIN_TARGET, 1)) != hipSuccess)
-                return fail(h, LOOPSPEC_EHIP, hipGetErrorString(e));
-        }
-    }
-    // the prompt's ids at positions 0..n-1 of the sequence's token record
-    // (committed tokens follow them), for loopspec_debug_branch
-    HIPCHK(h, hipStreamSynchronize(h->st));
-    std::memcpy(h->pin, ids, 4 * (size_t)n);
-    HIPCHK(h, hipMemcpyAsync(s.Y + (size_t)seq * h->d.max_ctx, h->pin, 4 * (size_t)n, hipMemcpyHostToDevice, h->st));
+    // the last block of the last position at depth R, then its readout
+    const int stack = Lc ? STACK_CODA : STACK_CORE;
+    e = launch_prefill_row(h->g, h->X + (size_t)(Lc > 1 ? h->xrow_pf_coda : h->xrow_pf) * h->g.h, m_last - 1,
+                           h->X + (size_t)h->xrow_last * h->g.h, h->st);
+    if (e == hipSuccess) e = launch_gather(h->g, h->pf_last, h->pf_one, 1, h->X, h->pb, h->bf16, h->st);
+    for (int k = 0; k < 5 && e == hipSuccess; ++k)
+        e = enqueue_kernel(h, k, stack, (Lc ? Lc : h->g.Lb) - 1, h->pf_last, h->pf_one, 1, true);
+    if (e == hipSuccess) e = enqueue_head(h, h->pf_last, h->pf_one, 1);
+    Sched t = s;
+    t.rowsC = h->pf_last;
+    t.nC = h->pf_one;
+    if (e == hipSuccess) e = enqueue_finalize(h, t, FIN_TARGET, 1);
+    if (e != hipSuccess) return fail(h, LOOPSPEC_EHIP, hipGetErrorString(e));
     int r = init_seq(h, seq, n, s.ro_tok);
     if (r) return r;
     int32_t tok = -1;
@@ -1335,7 +1416,7 @@ int loopspec_set_depths(loopspec_t h, int32_t d1, int32_t d2) {
         if (h->prompt_len[q] <= 0) continue;
         if ((e = launch_sched(s, OP_RESET, q, 0, nullptr, h->st)) != hipSuccess ||
             (e = launch_embed(h->g, s.js, s.njs, 1, h->embed, h->bf16, h->X, h->st)) != hipSuccess ||
-            (h->g.Lp && (e = enqueue_stack(h, STACK_PRE, s.rowsP, s.nP, h->S, false)) != hipSuccess))
+            (h->g.Lp && (e = enqueue_stack(h, STACK_PRE, s.rowsP, s.nP, h->S)) != hipSuccess))
             return fail(h, LOOPSPEC_EHIP, hipGetErrorString(e));
     }
     drop_graphs(h);
@@ -1492,10 +1573,10 @@ int loopspec_debug_readout(loopspec_t h, int32_t slot, int32_t depth, float* log
         // through the same launches a decode step uses (batch-invariant kernels:
         // the keys and values it rewrites are the ones already there)
         e = launch_embed(h->g, h->pf_jobs, one, 1, h->embed, h->bf16, h->X, h->st);
-        if (e == hipSuccess && h->g.Lp) e = enqueue_stack(h, STACK_PRE, rd, one, h->S, false);
-        for (int d = 1; d <= depth && e == hipSuccess; ++d) e = enqueue_stack(h, STACK_CORE, rd + d, one, h->S, false);
+        if (e == hipSuccess && h->g.Lp) e = enqueue_stack(h, STACK_PRE, rd, one, h->S);
+        for (int d = 1; d <= depth && e == hipSuccess; ++d) e = enqueue_stack(h, STACK_CORE, rd + d, one, h->S);
     }
-    if (e == hipSuccess && h->g.Lc) e = enqueue_stack(h, STACK_CODA, rd + R + 1, one, h->S, false);
+    if (e == hipSuccess && h->g.Lc) e = enqueue_stack(h, STACK_CODA, rd + R + 1, one, h->S);
     if (e == hipSuccess) e = enqueue_head(h, rd + R + 1, one, h->S);
     if (e != hipSuccess) return fail(h, LOOPSPEC_EHIP, hipGetErrorString(e));
     HIPCHK(h, hipMemcpyAsync(logits, h->logits, 4 * (size_t)h->d.vocab, hipMemcpyDeviceToHost, h->st));

@@ -1,0 +1,58 @@
+"""GPU: prompt passes at the edges of their tiles, against the fp64 oracle.
+
+The readouts after a prompt depend on every key and value that its pass wrote,
+at every depth: one teacher-forced position behind the prompt is compared at
+all depths, and the prompt's own first token.  Tolerances are the logits'
+(gpu_common.TOL: fp16 operands with fp32 sums, or fp32 throughout)."""
+import numpy as np
+import pytest
+
+import synth
+from gpu_common import MARGIN, TOL, log, model, oracle_lm, prompt
+from oracle import model as OM
+from paper_2609_17184_amd import Decoder
+
+pytestmark = pytest.mark.gpu
+
+
+def check(spec, w, lm, n, max_ctx):
+    pr = [int(t) for t in prompt(spec, n)]
+    log(f"[prefill] {spec.hidden} wide {spec.weight_dtype}, {n} positions")
+    node = lm.prefill(pr)
+    z0 = lm.logits(node, spec.R)
+    d2 = 2 if spec.R > 2 else 0
+    dec = Decoder(spec, w, R=spec.R, d1=1, d2=d2, max_seqs=1, max_ctx=max_ctx)
+    tok = int(np.argmax(z0))
+    first = dec.prefill(0, pr)
+    top = np.sort(z0)[-2:]
+    if top[1] - top[0] > MARGIN[spec.weight_dtype]:
+        assert first == tok
+    lg, _ = dec.forced_readout(0, [tok])
+    node = lm.extend(node, tok)
+    for r in range(1, spec.R + 1):
+        err = float(np.abs(lg[0, r - 1] - lm.logits(node, r)).max())
+        assert err < TOL[spec.weight_dtype], (n, r, err)
+    dec.close()
+
+
+@pytest.mark.parametrize("name", ["tiny", "small_bf16", "small_raven"])
+@pytest.mark.parametrize("n", [1, 2, 16, 17, 63, 64, 65, 129])
+def test_prompt_lengths(name, n):
+    """Row tiles of 16 and blocks of 64, one row short, full and one over; keys of 64 positions."""
+    spec, w = model(name)
+    check(spec, w, oracle_lm(name), n, 160)
+
+
+@pytest.mark.parametrize("n", [2048, 2049, 2111])
+def test_prompt_of_several_passes(n):
+    """A pass holds 2048 positions: the next one reads the first one's keys and values."""
+    spec, w = model("small_raven", R=2)
+    check(spec, w, oracle_lm("small_raven", R=2), n, 2200)
+
+
+def test_prompt_tiles_of_128():
+    """Every GEMM of a block over 2000 rows at this width has 256 tiles of 128 x 128, the rule's threshold,
+    the last row block ragged."""
+    spec = synth.ModelSpec(2048, 16, 128, 1024, 512, 0, 1, 0, R=2, alpha=0.3)
+    w = synth.make_weights(spec, seed=0)
+    check(spec, w, OM.LoopedLM(spec, w), 2000, 2048)
