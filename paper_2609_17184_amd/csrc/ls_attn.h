@@ -25,7 +25,7 @@ hipError_t attention_prepare(int lds_bytes);   // allow the dynamic LDS size
 // part != NULL: the shared-prefix task attention (part: its partials; cnt:
 // [rows][heads] counters, zero between launches); else one workgroup per (head, row)
 hipError_t launch_attention(const AttnParams& p, bool bf16, int m_cap, float* part, unsigned* cnt, hipStream_t st);
-// the M rows of a prompt pass (positions p0 .. p0 + M - 1 of a sequence at one depth)
-hipError_t launch_attention_prompt(const AttnParams& p, bool bf16, int seq, int p0, int depth, int M, hipStream_t st);
+// the M rows of an fp32 model's prompt pass (positions p0 .. p0 + M - 1 of a sequence at one depth)
+hipError_t launch_attention_prompt(const AttnParams& p, int seq, int p0, int depth, int M, hipStream_t st);
 
 }  // namespace ls

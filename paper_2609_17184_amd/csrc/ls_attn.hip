@@ -29,9 +29,10 @@ __global__ void __launch_bounds__(512) k_attn(AttnParams p) {
     attn_item<WT, DH, false>(p, row_head(p.rows, m), p.rows[m].anc, m, blockIdx.x, smem);
 }
 
-// The same over the rows of a prompt pass: row m is position p0 + m, and every
-// key and value it reads, its own included, is in the committed cache.
-template <typename WT, int DH>
+// The same over the rows of a prompt pass of an fp32 model (16-bit ones have a
+// kernel of their own, ls_prefill.hip): row m is position p0 + m, and every key
+// and value it reads, its own included, is in the committed cache.
+template <int DH>
 __global__ void __launch_bounds__(512) k_attn_prompt(AttnParams p, int seq, int p0, int depth) {
     extern __shared__ float smem[];
     const int m = blockIdx.y;
@@ -40,7 +41,7 @@ __global__ void __launch_bounds__(512) k_attn_prompt(AttnParams p, int seq, int 
     row.seq = seq;
     row.pos = row.tdone = p0 + m;
     row.depth = depth;
-    attn_item<WT, DH, false, true>(p, row, nullptr, m, blockIdx.x, smem);
+    attn_item<float, DH, false, true>(p, row, nullptr, m, blockIdx.x, smem);
 }
 
 // Shared-prefix task attention for decode row lists (KV cache management of
@@ -366,16 +367,19 @@ static hipError_t launch_t(const AttnParams& p, int m_cap, float* part, unsigned
 
 template <typename WT>
 static hipError_t allow(int bytes) {
-    const void* f[] = {(const void*)k_attn<WT, 16>,        (const void*)k_attn<WT, 32>,
-                       (const void*)k_attn<WT, 64>,        (const void*)k_attn_prompt<WT, 16>,
-                       (const void*)k_attn_prompt<WT, 32>, (const void*)k_attn_prompt<WT, 64>};
+    const void* f[] = {(const void*)k_attn<WT, 16>, (const void*)k_attn<WT, 32>, (const void*)k_attn<WT, 64>};
     for (const void* x : f) {
         hipError_t e = hipFuncSetAttribute(x, hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
         if (e != hipSuccess) return e;
     }
     if constexpr (sizeof(WT) == 2) {
-        const void* g[] = {(const void*)k_attn<WT, 96>, (const void*)k_attn<WT, 128>,
-                           (const void*)k_attn_prompt<WT, 96>, (const void*)k_attn_prompt<WT, 128>};
+        const void* g[] = {(const void*)k_attn<WT, 96>, (const void*)k_attn<WT, 128>};
+        for (const void* x : g) {
+            hipError_t e = hipFuncSetAttribute(x, hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
+            if (e != hipSuccess) return e;
+        }
+    } else {
+        const void* g[] = {(const void*)k_attn_prompt<16>, (const void*)k_attn_prompt<32>, (const void*)k_attn_prompt<64>};
         for (const void* x : g) {
             hipError_t e = hipFuncSetAttribute(x, hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
             if (e != hipSuccess) return e;
@@ -389,23 +393,18 @@ hipError_t attention_prepare(int lds_bytes) {
     return e != hipSuccess ? e : allow<float>(lds_bytes);
 }
 
-template <typename WT, int DH>
+template <int DH>
 static hipError_t launch_prompt_dh(const AttnParams& p, int seq, int p0, int depth, int M, hipStream_t st) {
-    hipLaunchKernelGGL((k_attn_prompt<WT, DH>), dim3(p.g.H, M), dim3(64 * attention_waves(p.chunks_cap)),
+    hipLaunchKernelGGL((k_attn_prompt<DH>), dim3(p.g.H, M), dim3(64 * attention_waves(p.chunks_cap)),
                        attention_lds_bytes(p.chunks_cap, DH), st, p, seq, p0, depth);
     return hipGetLastError();
 }
 
-hipError_t launch_attention_prompt(const AttnParams& p, bool bf16, int seq, int p0, int depth, int M, hipStream_t st) {
+hipError_t launch_attention_prompt(const AttnParams& p, int seq, int p0, int depth, int M, hipStream_t st) {
     switch (p.g.dh) {
-        case 16: return bf16 ? launch_prompt_dh<uint16_t, 16>(p, seq, p0, depth, M, st)
-                             : launch_prompt_dh<float, 16>(p, seq, p0, depth, M, st);
-        case 32: return bf16 ? launch_prompt_dh<uint16_t, 32>(p, seq, p0, depth, M, st)
-                             : launch_prompt_dh<float, 32>(p, seq, p0, depth, M, st);
-        case 64: return bf16 ? launch_prompt_dh<uint16_t, 64>(p, seq, p0, depth, M, st)
-                             : launch_prompt_dh<float, 64>(p, seq, p0, depth, M, st);
-        case 96: return bf16 ? launch_prompt_dh<uint16_t, 96>(p, seq, p0, depth, M, st) : hipErrorInvalidValue;
-        case 128: return bf16 ? launch_prompt_dh<uint16_t, 128>(p, seq, p0, depth, M, st) : hipErrorInvalidValue;
+        case 16: return launch_prompt_dh<16>(p, seq, p0, depth, M, st);
+        case 32: return launch_prompt_dh<32>(p, seq, p0, depth, M, st);
+        case 64: return launch_prompt_dh<64>(p, seq, p0, depth, M, st);
     }
     return hipErrorInvalidValue;
 }

@@ -36,7 +36,7 @@ struct PrefillGemm {
     void* XBout;
     float* SSQout;
     void* act;             // SWIGLU: [M][F] operand order
-    float* q;              // QKV: [M][h] rotated queries
+    void* q;               // QKV: [M][h] rotated queries, compute dtype, row-major
     void* kvc;             // QKV: committed cache
     int table;             // QKV: key/value table of the block at this depth
     const float* rope;
@@ -44,6 +44,17 @@ struct PrefillGemm {
 
 hipError_t prefill_prepare();   // allow the kernels' LDS sizes
 hipError_t launch_prefill_gemm(const PrefillGemm& p, int epi, bool bf16, hipStream_t st);
+
+// Causal attention of the rows of a 16-bit model's prompt pass over positions
+// 0 .. p0 + m of their table in the committed cache.
+struct PrefillAttn {
+    Geo g;
+    int M, p0, seq, table;
+    const void* q;         // [M][h] row-major
+    const void* kvc;
+    void* out;             // [M][h] operand order
+};
+hipError_t launch_prefill_attn(const PrefillAttn& p, hipStream_t st);
 
 // X[m] = E[tok[m]], its rounded copy and tile sums of squares, for M prompt rows
 hipError_t launch_prefill_embed(const Geo& g, const int32_t* tok, int M, const void* E, bool bf16, float* X,

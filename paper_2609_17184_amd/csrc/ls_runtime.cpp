@@ -1037,16 +1037,30 @@ hipError_t enqueue_prompt_block(loopspec_t h, int stack, int l, int depth, int s
     p.tiles = 3 * th - p.tile0;
     p.table = kv_table(h->g, stack, l, depth);
     if ((e = launch_prefill_gemm(p, EPI_QKV, h->bf16, h->st)) != hipSuccess || kv_only) return e;
-    AttnParams a{};
-    a.g = h->g;
-    a.q = h->qbuf;
-    a.kvc = h->kvc;
-    a.kvs = h->kvs;
-    a.stack = stack;
-    a.layer = l;
-    a.chunks_cap = h->chunks_cap;
-    a.out = h->att;
-    if ((e = launch_attention_prompt(a, h->bf16, seq, p0, depth, m, h->st)) != hipSuccess) return e;
+    if (h->bf16) {
+        PrefillAttn a{};
+        a.g = h->g;
+        a.M = m;
+        a.p0 = p0;
+        a.seq = seq;
+        a.table = p.table;
+        a.q = h->qbuf;
+        a.kvc = h->kvc;
+        a.out = h->att;
+        e = launch_prefill_attn(a, h->st);
+    } else {
+        AttnParams a{};
+        a.g = h->g;
+        a.q = h->qbuf;
+        a.kvc = h->kvc;
+        a.kvs = h->kvs;
+        a.stack = stack;
+        a.layer = l;
+        a.chunks_cap = h->chunks_cap;
+        a.out = h->att;
+        e = launch_attention_prompt(a, seq, p0, depth, m, h->st);
+    }
+    if (e != hipSuccess) return e;
     p.A = h->att;
     p.Wp = w.o;
     p.tile0 = 0;

@@ -56,3 +56,19 @@ def test_prompt_tiles_of_128():
     spec = synth.ModelSpec(2048, 16, 128, 1024, 512, 0, 1, 0, R=2, alpha=0.3)
     w = synth.make_weights(spec, seed=0)
     check(spec, w, OM.LoopedLM(spec, w), 2000, 2048)
+
+
+@pytest.mark.parametrize("dh", [16, 32, 64])
+@pytest.mark.parametrize("n", [15, 64, 130])
+def test_prompt_head_sizes(dh, n):
+    """The causal attention of a 16-bit prompt for the head sizes the presets do not have (96 and 128 are above)."""
+    spec = synth.ModelSpec(128, 128 // dh, dh, 256, 304, 0, 2, 0, R=3, alpha=0.3)
+    w = synth.make_weights(spec, seed=0)
+    check(spec, w, OM.LoopedLM(spec, w), n, 160)
+
+
+def test_prompt_of_many_query_blocks():
+    """32 queries per wave from 256 blocks of 128 on: 2100 positions of 16 heads, keys of 33 tiles, two passes."""
+    spec = synth.ModelSpec(256, 16, 16, 256, 304, 0, 1, 0, R=2, alpha=0.3)
+    w = synth.make_weights(spec, seed=0)
+    check(spec, w, OM.LoopedLM(spec, w), 2100, 2200)
