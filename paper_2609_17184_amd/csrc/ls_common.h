@@ -156,15 +156,42 @@ __device__ __forceinline__ float f_value(float v) {
 // Consumers test every fragment of every poll round, so the test is a few
 // instructions rather than one compare per element.
 typedef uint16_t u16x2 __attribute__((ext_vector_type(2)));
+// (The words are copied out first: the compiler takes a bit cast of a vector's
+// element for a cast of its first element.)
 __device__ __forceinline__ bool sentinel16(const u32x4& u) {
+    const uint32_t w0 = u[0], w1 = u[1], w2 = u[2], w3 = u[3];
     const u16x2 m = __builtin_elementwise_max(
-        __builtin_elementwise_max(__builtin_bit_cast(u16x2, u[0]), __builtin_bit_cast(u16x2, u[1])),
-        __builtin_elementwise_max(__builtin_bit_cast(u16x2, u[2]), __builtin_bit_cast(u16x2, u[3])));
+        __builtin_elementwise_max(__builtin_bit_cast(u16x2, w0), __builtin_bit_cast(u16x2, w1)),
+        __builtin_elementwise_max(__builtin_bit_cast(u16x2, w2), __builtin_bit_cast(u16x2, w3)));
     return __builtin_elementwise_max(m.x, m.y) == 0xFFFFu;
 }
 __device__ __forceinline__ bool sentinel32(const u32x4& u) {
     const uint32_t a = u[0] > u[1] ? u[0] : u[1], b = u[2] > u[3] ? u[2] : u[3];
     return (a > b ? a : b) == kSentinel;
+}
+// Some element of N fragments is the sentinel: one running maximum over all of
+// their words and a single test of it (about as many instructions as testing
+// one word of each fragment on its own).
+template <bool BF16, int N>
+__device__ __forceinline__ bool sentinel_any(const u32x4 (&u)[N]) {
+    if constexpr (BF16) {
+        u16x2 m = {0, 0};
+#pragma unroll
+        for (int i = 0; i < N; ++i)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const uint32_t w = u[i][e];
+                m = __builtin_elementwise_max(m, __builtin_bit_cast(u16x2, w));
+            }
+        return __builtin_elementwise_max(m.x, m.y) == 0xFFFFu;
+    } else {
+        uint32_t m = 0;
+#pragma unroll
+        for (int i = 0; i < N; ++i)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) m = u[i][e] > m ? u[i][e] : m;
+        return m == kSentinel;
+    }
 }
 // true once the launch gave up waiting (checked every 64 polls)
 __device__ __forceinline__ bool poll_abort(unsigned n, int32_t* err) {

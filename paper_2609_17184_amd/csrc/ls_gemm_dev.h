@@ -501,13 +501,10 @@ __device__ __forceinline__ void gemm_finish(const GemmParams& p, int item, int M
         // fragments not yet written by their producers are read again, all of
         // them in the same round (one round trip per round)
         for (unsigned n = 0;; ++n) {
-            bool miss[MAXS], any = false;
+            if (!__any(sentinel_any<sizeof(WT) == 2, MAXS>(a)) || poll_abort(n, p.err)) break;
+            bool miss[MAXS];
 #pragma unroll
-            for (int i = 0; i < MAXS; ++i) {
-                miss[i] = __any(sizeof(WT) == 2 ? sentinel16(a[i]) : sentinel32(a[i]));
-                any |= miss[i];
-            }
-            if (!any || poll_abort(n, p.err)) break;
+            for (int i = 0; i < MAXS; ++i) miss[i] = __any(sizeof(WT) == 2 ? sentinel16(a[i]) : sentinel32(a[i]));
             __builtin_amdgcn_s_sleep(1);
 #pragma unroll
             for (int i = 0; i < MAXS; ++i)
