@@ -442,10 +442,7 @@ def main():
     slots = dec.capacity()[0]
     kname = KERNEL_NAME[kind]
     if kind == "gate_up" and slots > 16:
-        # launches of up to 64 rows: stream-K from 64 MB of weights, else the 64-row tiles
-        kname = ("k_gemm_sk<SWIGLU, 32 or 64 rows>: RMSNorm + gate/up + SwiGLU of a core block (stream-K weight "
-                 "stream, row tiles per wave)" if 2 * F * h * wb >= (64 << 20) else
-                 "k_gemm<SWIGLU, 64 rows>: RMSNorm + gate/up + SwiGLU of a core block (64-row LDS tiles)")
+        kname = "k_gemm_rows<SWIGLU>: RMSNorm + gate/up + SwiGLU of a core block (weight stream of 17 to 64 rows)"
     if (kind == "gate_up" and slots <= 16 and gemm_sources_sha1() == GU_TRAFFIC["sources_sha1"]
             and a.model == GU_TRAFFIC["model"]):
         traffic = GU_TRAFFIC["bytes"]

@@ -13,7 +13,8 @@ struct AttnParams {
     const void* kvs;           // slot cache [slot][T][2][h]
     int stack, layer;
     int chunks_cap;            // ceil(max_ctx / 64)
-    void* out;                 // [M][h] attention output (weight dtype)
+    void* out;                 // [M][h] attention output (compute dtype), row-major or
+    int opd;                   // 1: in operand order (opd_elem)
     int32_t* err;              // persistent pass: kErrPoll when a read gave up waiting
 };
 

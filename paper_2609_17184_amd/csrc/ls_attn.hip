@@ -41,7 +41,7 @@ __global__ void __launch_bounds__(512) k_attn_prompt(AttnParams p, int seq, int 
     row.seq = seq;
     row.pos = row.tdone = p0 + m;
     row.depth = depth;
-    attn_item<float, DH, false, true>(p, row, nullptr, m, blockIdx.x, smem);
+    attn_item<float, DH, false>(p, row, nullptr, m, blockIdx.x, smem);
 }
 
 // Shared-prefix task attention for decode row lists (KV cache management of
@@ -119,7 +119,7 @@ __device__ __forceinline__ void combine_partials(const AttnParams& p, int m, int
         const int d = lane + 64 * j;
         if (d >= DH) break;
         const float r = o[j] / lsum;
-        const size_t idx = (size_t)m * p.g.h + head * DH + d;
+        const size_t idx = attn_out<WT, false>(p, m, head * DH + d);
         if (sizeof(WT) == 2)
             ((uint16_t*)p.out)[idx] = f2h(r);
         else

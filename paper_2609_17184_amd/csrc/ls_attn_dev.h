@@ -4,7 +4,6 @@
 #pragma once
 #include "ls_attn.h"
 #include "ls_gemm_dev.h"   // buffer resources
-#include "ls_prefill.h"    // operand order
 
 namespace ls {
 
@@ -39,6 +38,12 @@ __device__ __forceinline__ float exp2_fast(float x) { return __builtin_amdgcn_ex
 // fp16 pair dot product accumulated in fp32 (v_dot2_f32_f16): acc + a.lo*b.lo + a.hi*b.hi
 __device__ __forceinline__ float dot2_f16(uint32_t a, uint32_t b, float acc) {
     return __builtin_amdgcn_fdot2(__builtin_bit_cast(f16x2, a), __builtin_bit_cast(f16x2, b), acc, false);
+}
+
+// Index of output element k of row m (p.opd: operand order, never in the persistent pass)
+template <typename WT, bool COH>
+__device__ __forceinline__ size_t attn_out(const AttnParams& p, int m, int k) {
+    return !COH && p.opd ? opd_elem<WT>(m, k, p.g.h) : (size_t)m * p.g.h + k;
 }
 
 // Address of one head's keys (kv = 0) or values (kv = 1) at one position of a row.
@@ -350,8 +355,7 @@ __device__ __forceinline__ void attn_own(const AttnParams& p, const Row& row_in,
     l_out = 1.f;
 }
 
-// OPD: the output goes to p.out in MFMA operand order (prompt rows), else row-major
-template <typename WT, int DH, bool COH, bool OPD = false>
+template <typename WT, int DH, bool COH>
 __device__ __forceinline__ void attn_combine_lds(const AttnParams& p, int m, int head, int n, const float* smem);
 
 // One (row m, head) item by the whole workgroup: its waves take the chunks of
@@ -360,7 +364,7 @@ __device__ __forceinline__ void attn_combine_lds(const AttnParams& p, int m, int
 // partials are combined in LDS in chunk order.  COH: inside the persistent
 // pass (device-scope query, own key / value and output).
 // LDS: [chunks + 1][DH + 2] partials.
-template <typename WT, int DH, bool COH, bool OPD = false>
+template <typename WT, int DH, bool COH>
 __device__ __forceinline__ void attn_item(const AttnParams& p, const Row& row, const int* anc, int m, int head,
                                           float* smem) {
     using A = AttnGeo<WT, DH>;
@@ -386,7 +390,7 @@ __device__ __forceinline__ void attn_item(const AttnParams& p, const Row& row, c
         }
     }
     __syncthreads();
-    attn_combine_lds<WT, DH, COH, OPD>(p, m, head, n, smem);
+    attn_combine_lds<WT, DH, COH>(p, m, head, n, smem);
     __syncthreads();
 }
 
@@ -395,7 +399,7 @@ __device__ __forceinline__ void attn_item(const AttnParams& p, const Row& row, c
 // sums its chunk values and the weight sums with them in chunk order
 // (partials in groups of CB: every LDS read of a group is issued before any
 // is used; partials past n read partial 0 and weigh nothing).
-template <typename WT, int DH, bool COH, bool OPD>
+template <typename WT, int DH, bool COH>
 __device__ __forceinline__ void attn_combine_lds(const AttnParams& p, int m, int head, int n, const float* smem) {
     const int tid = tid_local();
     constexpr int CB = 8;
@@ -427,7 +431,7 @@ __device__ __forceinline__ void attn_combine_lds(const AttnParams& p, int m, int
             }
         }
         const float r = o / l;
-        const size_t idx = OPD ? prefill_elem<WT>(m, head * DH + d, p.g.h) : (size_t)m * p.g.h + head * DH + d;
+        const size_t idx = attn_out<WT, COH>(p, m, head * DH + d);
         if (sizeof(WT) == 2)
             st_u16<COH>((uint16_t*)p.out + idx, COH ? h_value(r) : f2h(r));
         else

@@ -283,8 +283,18 @@ __device__ __forceinline__ float ssq16(const float* v) {
     return s;
 }
 
+// Activations of prompt passes and of decode passes of more than 16 rows are
+// stored in MFMA operand order: fragments of 16 rows x one k step (32 fp16 or
+// 16 fp32 columns) of 1 KB, row tile by row tile, lane l of a fragment holding
+// 16 bytes of row l % 16.  Index of element (m, k) of a buffer of K columns:
+template <typename WT>
+__device__ __forceinline__ size_t opd_elem(int m, int k, int K) {
+    constexpr int VEC = 16 / sizeof(WT), KSTEP = 4 * VEC;
+    return ((size_t)(m / 16) * (K / KSTEP) + k / KSTEP) * (64 * VEC) + ((k % KSTEP) / VEC * 16 + m % 16) * VEC + k % VEC;
+}
+
 // Pass buffers, in row order of the pass's row list:
-//   XB   [rows][h]         hidden state rounded to the weight dtype (GEMM A operand)
+//   XB   [rows][h]         hidden state rounded to the weight dtype (GEMM A operand), row-major or in operand order
 //   SSQR [rows][h/16]      sums of squares per 16-column tile of the fp32 state
 struct PassBuf {
     void* XB;

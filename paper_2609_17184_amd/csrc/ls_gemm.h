@@ -7,12 +7,10 @@ namespace ls {
 enum Epi { EPI_QKV = 0, EPI_RESID = 1, EPI_SWIGLU = 2, EPI_LOGITS = 3 };
 enum AMode { A_NORM = 0, A_BUF = 1 };
 
-// k steps (one 16-byte weight load per lane each) a wavefront keeps in flight
-// for an epilogue kind and NTM 16-row tiles of accumulators (register budget:
-// the residual GEMMs hold no RMSNorm statistics, gate/up streams two matrices)
-__host__ __device__ constexpr int gemm_max_steps(int epi, int ntm) {
-    return ntm > 1 ? (epi == EPI_SWIGLU ? 4 : 8) : (epi == EPI_RESID ? 12 : 8);
-}
+// k steps (one 16-byte weight load per lane each) a wavefront of the direct
+// path keeps in flight for an epilogue kind (register budget: the residual
+// GEMMs hold no RMSNorm statistics)
+__host__ __device__ constexpr int gemm_max_steps(int epi) { return epi == EPI_RESID ? 12 : 8; }
 
 struct GemmParams {
     Geo g;
@@ -29,7 +27,7 @@ struct GemmParams {
     const void* Wp;
     int N_mat;                 // output features per matrix
     int tiles;                 // 16-column tiles in the launch
-    int tpw, ks, kc;           // tiles per workgroup, k-slices (waves) per workgroup, LDS k chunk (64-row variant)
+    int tpw, ks;               // direct path and persistent pass: tiles, k-slices (waves) per workgroup
     // split k across workgroups (direct path, tpw = 1): kg workgroups per tile,
     // each summing its ks slices; the last of them to finish (counted on
     // cnt[tile]) sums the kg partials in workgroup order and runs the
@@ -64,15 +62,18 @@ size_t packed_elems(int epi, int N_mat, int K, bool bf16);
 hipError_t launch_pack(int epi, const void* const* W, const void* gain, void* out, int N_mat, int K, const Geo& g,
                        bool bf16, int32_t* err, hipStream_t st);
 
-size_t gemm_lds_bytes(int wbytes, int epi, int nmat, int tpw, int ks, int kc, int nt_max, int kg = 1);
+size_t gemm_lds_bytes(int nmat, int tpw, int ks, int kg);
 hipError_t gemm_prepare(int lds_bytes);   // allow the dynamic LDS size on every instantiation
-hipError_t launch_gemm(const GemmParams& p, int epi, bool bf16, int nt_max, hipStream_t st);
+hipError_t launch_gemm(const GemmParams& p, int epi, bool bf16, hipStream_t st);
 
 // Stream-K launches of at most 16 rows (ls_gemm_sk.hip): the grid that keeps
 // every workgroup resident, and the most waves a tile can be split over (the
 // partial slots per tile: p.kg of a launch, p.part holds tiles x kg x NMAT x
 // 256 floats, p.cnt one counter per tile).
-hipError_t gemm_sk_shape(int epi, bool bf16, int nt, int tiles, int K, int* grid, int* contrib);
-hipError_t launch_gemm_sk(const GemmParams& p, int epi, bool bf16, int nt, int grid, hipStream_t st);
+hipError_t gemm_sk_shape(int epi, bool bf16, int tiles, int K, int* grid, int* contrib);
+hipError_t launch_gemm_sk(const GemmParams& p, int epi, bool bf16, int grid, hipStream_t st);
+
+// Launches of 17 to 64 rows (ls_gemm_rows.hip); activations in operand order
+hipError_t launch_gemm_rows(const GemmParams& p, int epi, bool bf16, int rows_cap, hipStream_t st);
 
 }  // namespace ls

@@ -66,7 +66,7 @@ struct WaveGeo {
 
 __host__ __device__ __forceinline__ int gemm_kg(const GemmParams& p) { return p.kg > 1 ? p.kg : 1; }
 
-template <typename WT, bool CONTIG>
+template <typename WT>
 __device__ __forceinline__ WaveGeo wave_geo(const GemmParams& p, int item, int kgi = 0) {
     WaveGeo w;
     const int tid = tid_local();
@@ -79,22 +79,11 @@ __device__ __forceinline__ WaveGeo wave_geo(const GemmParams& p, int item, int k
     w.j = w.lane & 15;
     w.grp = w.lane >> 4;
     w.nsteps = p.K / WTraits<WT>::KSTEP;
-    if (CONTIG) {   // a contiguous block of steps per wave
-        const unsigned KS = (unsigned)(p.ks * gemm_kg(p)), gs = (unsigned)(kgi * p.ks + w.ksl);
-        w.s0 = (int)((unsigned)w.nsteps * gs / KS);
-        w.nst = (int)((unsigned)w.nsteps * (gs + 1) / KS) - w.s0;
-    } else {        // every ks-th step (all waves share staged activation chunks)
-        w.s0 = 0;
-        w.nst = w.ksl < w.nsteps ? (w.nsteps - w.ksl + p.ks - 1) / p.ks : 0;
-    }
+    // a contiguous block of steps per wave
+    const unsigned KS = (unsigned)(p.ks * gemm_kg(p)), gs = (unsigned)(kgi * p.ks + w.ksl);
+    w.s0 = (int)((unsigned)w.nsteps * gs / KS);
+    w.nst = (int)((unsigned)w.nsteps * (gs + 1) / KS) - w.s0;
     return w;
-}
-
-// This wave's packed weight blocks: the tile's first block plus the lane offset.
-template <typename WT, int NMAT>
-__device__ __forceinline__ const WT* packed_tile(const GemmParams& p, const WaveGeo& w) {
-    constexpr int VEC = WTraits<WT>::VEC;
-    return (const WT*)p.Wp + (size_t)(w.tile_ok ? w.tile : 0) * w.nsteps * NMAT * 64 * VEC + w.lane * VEC;
 }
 
 // Buffer resource over [p, p + bytes): loads at offsets >= bytes return zero.
@@ -126,7 +115,7 @@ struct BRegs {
 template <typename WT, int NMAT, int MAXS>
 __device__ __forceinline__ void gemm_load_b(const GemmParams& p, int item, BRegs<WT, NMAT, MAXS>& R,
                                             bool live = true, int kgi = 0) {
-    const WaveGeo w = wave_geo<WT, true>(p, item, kgi);
+    const WaveGeo w = wave_geo<WT>(p, item, kgi);
     const bool ok = live && w.tile_ok;
     const char* base = (const char*)p.Wp + (ok ? ((size_t)w.tile * w.nsteps + w.s0) * NMAT * 1024 : 0);
     const __amdgpu_buffer_rsrc_t rs = buf_rsrc(base, ok ? (uint32_t)w.nst * NMAT * 1024 : 0u);
@@ -149,7 +138,7 @@ __device__ __forceinline__ void gemm_load_b(const GemmParams& p, int item, BRegs
 constexpr int kPfFrags = 16;
 template <typename WT, int NMAT, int MAXS>
 __device__ __forceinline__ void gemm_stage_b(const GemmParams& p, int item, char* lds_wave) {
-    const WaveGeo w = wave_geo<WT, true>(p, item);
+    const WaveGeo w = wave_geo<WT>(p, item);
     const bool ok = w.tile_ok;
     const char* base = (const char*)p.Wp + (ok ? ((size_t)w.tile * w.nsteps + w.s0) * NMAT * 1024 : 0);
     const __amdgpu_buffer_rsrc_t rs = buf_rsrc(base, ok ? (uint32_t)w.nst * NMAT * 1024 : 0u);
@@ -167,7 +156,7 @@ __device__ __forceinline__ void gemm_stage_b(const GemmParams& p, int item, char
 template <typename WT, int NMAT, int MAXS>
 __device__ __forceinline__ void gemm_load_b_staged(const GemmParams& p, int item, BRegs<WT, NMAT, MAXS>& R,
                                                    const char* lds_wave) {
-    const WaveGeo w = wave_geo<WT, true>(p, item);
+    const WaveGeo w = wave_geo<WT>(p, item);
     const bool ok = w.tile_ok;
     const char* base = (const char*)p.Wp + (ok ? ((size_t)w.tile * w.nsteps + w.s0) * NMAT * 1024 : 0);
     const __amdgpu_buffer_rsrc_t rs = buf_rsrc(base, ok ? (uint32_t)w.nst * NMAT * 1024 : 0u);
@@ -441,7 +430,7 @@ __device__ __forceinline__ void gemm_finish(const GemmParams& p, int item, int M
     constexpr int KSTEP = WTraits<WT>::KSTEP, VEC = WTraits<WT>::VEC;
     constexpr bool norm = EPI != EPI_RESID;
     constexpr int NSS = norm ? 4 : 1;
-    const WaveGeo w = wave_geo<WT, true>(p, item, kgi);
+    const WaveGeo w = wave_geo<WT>(p, item, kgi);
     const int tiles_h = p.g.ssq_tiles;
     // every operand load of the phase is issued before any is waited for:
     // sums of squares, the activation rows, the epilogue's first operand
@@ -541,7 +530,7 @@ __device__ __forceinline__ void gemm_direct(const GemmParams& p, int item, int k
     constexpr int KSTEP = WTraits<WT>::KSTEP, VEC = WTraits<WT>::VEC;
     constexpr bool norm = EPI != EPI_RESID;
     constexpr int NSS = norm ? 4 : 1;
-    const WaveGeo w = wave_geo<WT, true>(p, item, kgi);
+    const WaveGeo w = wave_geo<WT>(p, item, kgi);
     const int tiles_h = p.g.ssq_tiles;
     // (1) the row field the first epilogue operand's address needs
     const int it0 = tid_local();

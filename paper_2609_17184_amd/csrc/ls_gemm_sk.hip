@@ -1,5 +1,6 @@
-// Stream-K weight-streaming GEMM for launches of at most 16 NT rows (NT = 1,
-// 2 or 4 row tiles of 16: the decode's in-flight rows, up to 64).
+// Stream-K weight-streaming GEMM for launches of at most 16 rows (the decode's
+// in-flight rows of handles with at most 16 branch slots; ls_gemm_rows.hip runs
+// those of more).
 //
 // The packed weight matrix of a launch is one contiguous stream of 1 KB (per
 // matrix) fragments, tile after tile, k step after k step (launch_pack's
@@ -17,9 +18,8 @@
 // depth), RESID (residual add, rounded copy and per-tile sums of squares for
 // the next RMSNorm), SWIGLU (silu(g) * u) or LOGITS (logits, per-tile maximum
 // and its id).  The four waves of a workgroup are independent streams; their
-// one barrier, at the start, publishes the rows' 1/rms (and, for wider
-// launches, the rows' epilogue fields) that they compute together while their
-// first round is in flight.
+// one barrier, at the start, publishes the rows' 1/rms that they compute
+// together while their first round is in flight.
 #include <algorithm>
 
 #include "ls_gemm_dev.h"
@@ -27,8 +27,7 @@
 namespace ls {
 
 constexpr int kSkWaves = 4;
-constexpr int kSkMinSteps = 32;        // k steps per wave at least (16-row launches)
-constexpr int kSkMinStepsWide = 32;    // (launches of 32 or 64 rows)
+constexpr int kSkMinSteps = 32;        // k steps per wave at least
 
 __device__ __forceinline__ long long sk_wave_of(long long u, long long P, long long U) {
     return ((u + 1) * P - 1) / U;     // the wave whose range [U w / P, U (w+1) / P) holds unit u
@@ -43,9 +42,9 @@ __device__ __forceinline__ const void* sk_uniform(const void* p) {
     return (const void*)(((uint64_t)hi << 32) | lo);
 }
 
-template <typename WT, int NMAT, int S, int NT>
-__device__ __forceinline__ void sk_load(const GemmParams& p, int ns, long long u, int n, int lane, int M, int ntl,
-                                        u32x4 (&B)[S][NMAT], u32x4 (&A)[S][NT]) {
+template <typename WT, int NMAT, int S>
+__device__ __forceinline__ void sk_load(const GemmParams& p, int ns, long long u, int n, int lane, int M,
+                                        u32x4 (&B)[S][NMAT], u32x4 (&A)[S]) {
     constexpr int KSTEP = WTraits<WT>::KSTEP, VEC = WTraits<WT>::VEC;
     const int s = (int)(u % ns);
     // (n = 0: an empty range at any base, every load returns zeros)
@@ -57,20 +56,14 @@ __device__ __forceinline__ void sk_load(const GemmParams& p, int ns, long long u
     for (int i = 0; i < S; ++i)
 #pragma unroll
         for (int q = 0; q < NMAT; ++q) B[i][q] = buf_load16<2>(rb, i < n ? vb : kOutOfRange, (i * NMAT + q) * 1024);
-    // activation fragments of the same steps, 16 rows per row tile (rows >= M
-    // lie beyond the range: zeros; row tiles past the live ones are not read)
+    // activation fragments of the same steps (rows >= M lie beyond the range: zeros)
     const WT* a0 = (const WT*)p.abuf + (size_t)s * KSTEP;
     const __amdgpu_buffer_rsrc_t ra =
         buf_rsrc(sk_uniform(a0),
                  __builtin_amdgcn_readfirstlane(n ? (uint32_t)(((size_t)M * p.K - (size_t)s * KSTEP) * sizeof(WT)) : 0u));
     const int va = ((lane & 15) * p.K + (lane >> 4) * VEC) * (int)sizeof(WT);
-    const int rstride = 16 * p.K * (int)sizeof(WT);
 #pragma unroll
-    for (int i = 0; i < S; ++i)
-#pragma unroll
-        for (int rt = 0; rt < NT; ++rt)
-            A[i][rt] = buf_load16<0>(ra, (i < n && rt < ntl) ? va + rt * rstride : kOutOfRange,
-                                     i * KSTEP * (int)sizeof(WT));
+    for (int i = 0; i < S; ++i) A[i] = buf_load16<0>(ra, i < n ? va : kOutOfRange, i * KSTEP * (int)sizeof(WT));
 }
 
 // 1/rms of rows 0..M-1 into r[0..M) (workgroup LDS), from the per-tile sums
@@ -91,68 +84,52 @@ __device__ __forceinline__ void sk_rinv(const GemmParams& p, int M, int wv, int 
     }
 }
 
-// The row fields an epilogue reads, copied to LDS once per workgroup
-struct SkRowMeta {
-    int xrow, pos, slot, seq, depth;
-};
-
 // Epilogue operands of tile t loaded ahead of its finish: RESID the residual
 // values of the lane's rows, QKV the (cos, sin) of its RoPE pair per row.
-template <int NT>
 struct SkPre {
     int t;                 // tile they belong to (-1: none)
-    f32x4 a[NT], b[NT];
+    f32x4 a, b;
 };
 
-// (meta: the rows' fields in LDS, else null: read from the row list)
-template <int EPI, int NT>
-__device__ __forceinline__ SkPre<NT> sk_prefetch(const GemmParams& p, int t, int M, int lane,
-                                                 const SkRowMeta* meta = nullptr) {
-    SkPre<NT> r;
+template <int EPI>
+__device__ __forceinline__ SkPre sk_prefetch(const GemmParams& p, int t, int M, int lane) {
+    SkPre r;
     r.t = t;
     const int j = lane & 15, grp = lane >> 4;
 #pragma unroll
-    for (int rt = 0; rt < NT; ++rt)
-#pragma unroll
-        for (int v = 0; v < 4; ++v) {
-            r.a[rt][v] = 0.f;
-            r.b[rt][v] = 0.f;
-        }
+    for (int v = 0; v < 4; ++v) {
+        r.a[v] = 0.f;
+        r.b[v] = 0.f;
+    }
     if (EPI == EPI_RESID) {
 #pragma unroll
-        for (int rt = 0; rt < NT; ++rt)
-#pragma unroll
-            for (int v = 0; v < 4; ++v) {
-                const int m = rt * 16 + grp * 4 + v;
-                if (m < M) r.a[rt][v] = p.X[(size_t)(meta ? meta[m].xrow : p.rows[m].xrow) * p.g.h + t * 16 + j];
-            }
+        for (int v = 0; v < 4; ++v) {
+            const int m = grp * 4 + v;
+            if (m < M) r.a[v] = p.X[(size_t)p.rows[m].xrow * p.g.h + t * 16 + j];
+        }
     } else if (EPI == EPI_QKV) {
         const int tph = p.g.h / kTile, tpd = p.g.dh / kTile, half = p.g.dh / 2;
         const int mat = t / tph, lt = t - mat * tph, sub = lt - (lt / tpd) * tpd;
         if (mat < 2 && j < 8) {
 #pragma unroll
-            for (int rt = 0; rt < NT; ++rt)
-#pragma unroll
-                for (int v = 0; v < 4; ++v) {
-                    const int m = rt * 16 + grp * 4 + v;
-                    if (m < M) {
-                        const int pos = meta ? meta[m].pos : p.rows[m].pos;
-                        const float* rp = p.rope + ((size_t)pos * half + sub * 8 + j) * 2;
-                        r.a[rt][v] = rp[0];
-                        r.b[rt][v] = rp[1];
-                    }
+            for (int v = 0; v < 4; ++v) {
+                const int m = grp * 4 + v;
+                if (m < M) {
+                    const float* rp = p.rope + ((size_t)p.rows[m].pos * half + sub * 8 + j) * 2;
+                    r.a[v] = rp[0];
+                    r.b[v] = rp[1];
                 }
+            }
         }
     }
     return r;
 }
 
-// Epilogue of tile t over rows r0 .. r0+15 from the wave's summed
-// accumulators: lane l holds rows r0 + 4 (l / 16) + v (v = 0..3) of column
-// l % 16 of each matrix.  have: pa / pb hold the prefetched operands.
+// Epilogue of tile t from the wave's summed accumulators: lane l holds rows
+// 4 (l / 16) + v (v = 0..3) of column l % 16 of each matrix.  have: pa / pb hold the prefetched operands.
 template <typename WT, int EPI, int NMAT>
-__device__ __forceinline__ void sk_finish(const GemmParams& p, int t, int M, int r0, int lane,
-                                          const f32x4 (&acc)[NMAT], const float* rinv, const SkRowMeta* meta,
+__device__ __forceinline__ void sk_finish(const GemmParams& p, int t, int M, int lane,
+                                          const f32x4 (&acc)[NMAT], const float* rinv,
                                           bool have, f32x4 pa, f32x4 pb) {
     constexpr bool BF = sizeof(WT) == 2;
     const int j = lane & 15, grp = lane >> 4;
@@ -164,17 +141,17 @@ __device__ __forceinline__ void sk_finish(const GemmParams& p, int t, int M, int
         float xin[4];
 #pragma unroll
         for (int v = 0; v < 4; ++v) {
-            const int m = r0 + grp * 4 + v;
-            xr[v] = m < M ? (meta ? meta[m].xrow : p.rows[m].xrow) : 0;
+            const int m = grp * 4 + v;
+            xr[v] = m < M ? p.rows[m].xrow : 0;
         }
 #pragma unroll
         for (int v = 0; v < 4; ++v) {
-            const int m = r0 + grp * 4 + v;
+            const int m = grp * 4 + v;
             xin[v] = have ? pa[v] : m < M ? p.X[(size_t)xr[v] * p.g.h + n] : 0.f;
         }
 #pragma unroll
         for (int v = 0; v < 4; ++v) {
-            const int m = r0 + grp * 4 + v;
+            const int m = grp * 4 + v;
             float out = 0.f;
             if (m < M) {
                 out = xin[v] + acc[0][v];
@@ -192,7 +169,7 @@ __device__ __forceinline__ void sk_finish(const GemmParams& p, int t, int M, int
     } else if (EPI == EPI_SWIGLU) {
 #pragma unroll
         for (int v = 0; v < 4; ++v) {
-            const int m = r0 + grp * 4 + v;
+            const int m = grp * 4 + v;
             if (m >= M) continue;
             const float r = rinv[m];
             const float gt = acc[0][v] * r, up = acc[NMAT - 1][v] * r;
@@ -211,31 +188,21 @@ __device__ __forceinline__ void sk_finish(const GemmParams& p, int t, int M, int
         float cs[4], sn[4];
 #pragma unroll
         for (int v = 0; v < 4; ++v) {
-            const int m = r0 + grp * 4 + v;
+            const int m = grp * 4 + v;
             pos[v] = slot[v] = seq[v] = dep[v] = 0;
             if (m < M) {
-                if (meta) {
-                    const SkRowMeta& r = meta[m];
-                    pos[v] = r.pos;
-                    if (mat > 0) {
-                        slot[v] = r.slot;
-                        seq[v] = r.seq;
-                        dep[v] = r.depth;
-                    }
-                } else {
-                    const Row& r = p.rows[m];
-                    pos[v] = r.pos;
-                    if (mat > 0) {
-                        slot[v] = r.slot;
-                        seq[v] = r.seq;
-                        dep[v] = r.depth;
-                    }
+                const Row& r = p.rows[m];
+                pos[v] = r.pos;
+                if (mat > 0) {
+                    slot[v] = r.slot;
+                    seq[v] = r.seq;
+                    dep[v] = r.depth;
                 }
             }
         }
 #pragma unroll
         for (int v = 0; v < 4; ++v) {
-            const int m = r0 + grp * 4 + v;
+            const int m = grp * 4 + v;
             cs[v] = pa[v];
             sn[v] = pb[v];
             if (!have && mat < 2 && j < 8 && m < M) {
@@ -245,7 +212,7 @@ __device__ __forceinline__ void sk_finish(const GemmParams& p, int t, int M, int
         }
 #pragma unroll
         for (int v = 0; v < 4; ++v) {
-            const int m = r0 + grp * 4 + v;
+            const int m = grp * 4 + v;
             const float x = m < M ? acc[0][v] * rinv[m] : 0.f;
             const float partner = __shfl_xor(x, 8);      // column j + 8 holds the pair's second half
             if (m >= M || j >= 8) continue;
@@ -276,7 +243,7 @@ __device__ __forceinline__ void sk_finish(const GemmParams& p, int t, int M, int
         const int n = t * 16 + j;
 #pragma unroll
         for (int v = 0; v < 4; ++v) {
-            const int m = r0 + grp * 4 + v;
+            const int m = grp * 4 + v;
             const bool live = m < M && n < p.N_mat;
             const float val = live ? acc[0][v] * rinv[m] : 0.f;
             if (live) {
@@ -303,16 +270,14 @@ __device__ __forceinline__ void sk_finish(const GemmParams& p, int t, int M, int
     }
 }
 
-template <typename WT, int EPI, int NMAT, int S, int NT>
-__global__ void __launch_bounds__(kSkWaves * 64) __attribute__((amdgpu_waves_per_eu(NT == 1 ? 1 : 2))) k_gemm_sk(GemmParams p) {
-    __shared__ float rinv[16 * NT];
-    __shared__ SkRowMeta meta[16 * NT];
-    const int M = min(ld_uniform(p.nrows), 16 * NT);       // (the host sizes NT from the row capacity)
+template <typename WT, int EPI, int NMAT, int S>
+__global__ void __launch_bounds__(kSkWaves * 64) __attribute__((amdgpu_waves_per_eu(1))) k_gemm_sk(GemmParams p) {
+    __shared__ float rinv[16];
+    const int M = min(ld_uniform(p.nrows), 16);
     if (M <= 0) return;
     // the wave index is wave-uniform: the stream geometry and the buffer
     // resources derived from it stay in scalar registers
     const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int ntl = NT == 1 ? 1 : (M + 15) / 16;           // live row tiles (M <= 16 NT)
     constexpr int KSTEP = WTraits<WT>::KSTEP;
     GemmParams q = p;
     if (EPI != EPI_RESID) q.abuf = p.XB;                   // the A operand of the normalised kinds
@@ -324,30 +289,15 @@ __global__ void __launch_bounds__(kSkWaves * 64) __attribute__((amdgpu_waves_per
         const long long r = min((long long)S, min(u1 - u, (long long)ns - u % ns));
         return (int)r;
     };
-    f32x4 acc[NT][NMAT];
+    f32x4 acc[NMAT];
 #pragma unroll
-    for (int rt = 0; rt < NT; ++rt)
-#pragma unroll
-        for (int k = 0; k < NMAT; ++k) acc[rt][k] = f32x4{0.f, 0.f, 0.f, 0.f};
+    for (int k = 0; k < NMAT; ++k) acc[k] = f32x4{0.f, 0.f, 0.f, 0.f};
     // the tile this wave may finish at the end of the launch (its last
     // segment's tile: every other contributor of it ends earlier or at the same
-    // time) has its epilogue operands loaded now (16-row launches: wider ones
-    // have no registers to hold them through the stream)
-    const SkPre<NT> pre = NT == 1 && u0 < u1 ? sk_prefetch<EPI, NT>(q, (int)((u1 - 1) / ns), M, lane) : SkPre<NT>{-1, {}, {}};
-    auto finish = [&](int t, const f32x4 (&a)[NT][NMAT]) __attribute__((always_inline)) {
-        if (NT > 1 && (EPI == EPI_RESID || EPI == EPI_QKV)) {
-            // the epilogue operands of every row tile in one round trip
-            const SkPre<NT> g = sk_prefetch<EPI, NT>(q, t, M, lane, meta);
-#pragma unroll
-            for (int rt = 0; rt < NT; ++rt)
-                if (rt < ntl) sk_finish<WT, EPI, NMAT>(q, t, M, rt * 16, lane, a[rt], rinv, meta, true, g.a[rt], g.b[rt]);
-        } else {
-#pragma unroll
-            for (int rt = 0; rt < NT; ++rt)
-                if (rt < ntl)
-                    sk_finish<WT, EPI, NMAT>(q, t, M, rt * 16, lane, a[rt], rinv, NT > 1 ? meta : nullptr, pre.t == t,
-                                             pre.a[rt], pre.b[rt]);
-        }
+    // time) has its epilogue operands loaded now
+    const SkPre pre = u0 < u1 ? sk_prefetch<EPI>(q, (int)((u1 - 1) / ns), M, lane) : SkPre{-1, {}, {}};
+    auto finish = [&](int t, const f32x4 (&a)[NMAT]) __attribute__((always_inline)) {
+        sk_finish<WT, EPI, NMAT>(q, t, M, lane, a, rinv, pre.t == t, pre.a, pre.b);
     };
     // the end of a tile segment: finish the tile, or hand the partial to the
     // tile's first contributor.  A tile shared by several waves is finished by
@@ -363,42 +313,35 @@ __global__ void __launch_bounds__(kSkWaves * 64) __attribute__((amdgpu_waves_per
         const int wlo = (int)sk_wave_of(a, P, U), nct = (int)sk_wave_of(b - 1, P, U) - wlo + 1;
         if (nct > 1) {
             const int k = (int)w - wlo, grp = lane >> 4, jj = lane & 15;
-            float* all = p.part + (size_t)t * p.kg * NT * NMAT * 256;
+            float* all = p.part + (size_t)t * p.kg * NMAT * 256;
             if (k != 0) {
-                float* part = all + (size_t)k * NT * NMAT * 256;
+                float* part = all + (size_t)k * NMAT * 256;
 #pragma unroll
-                for (int rt = 0; rt < NT; ++rt)
+                for (int m = 0; m < NMAT; ++m)
 #pragma unroll
-                    for (int m = 0; m < NMAT; ++m)
-#pragma unroll
-                        for (int v = 0; v < 4; ++v)
-                            if (rt * 16 + grp * 4 + v < M)
-                                st_f32<true>(part + (rt * NMAT + m) * 256 + (grp * 4 + v) * 16 + jj, f_value(acc[rt][m][v]));
+                    for (int v = 0; v < 4; ++v)
+                        if (grp * 4 + v < M) st_f32<true>(part + m * 256 + (grp * 4 + v) * 16 + jj, f_value(acc[m][v]));
                 return;
             }
             // the other partials added to the wave's own, CB contributors at a time (one round trip per
-            // CB, repeated while a slot still holds the sentinel; CB keeps the
-            // kernel's registers within its occupancy)
-            constexpr int CB = NT == 1 ? 2 : 1;
+            // CB, repeated while a slot still holds the sentinel)
+            constexpr int CB = 2;
             for (int c0 = 1; c0 < nct; c0 += CB) {
-                float x[CB][NT][NMAT][4];
+                float x[CB][NMAT][4];
                 for (unsigned n = 0;; ++n) {
                     bool miss = false;
 #pragma unroll
                     for (int cc = 0; cc < CB; ++cc)
 #pragma unroll
-                        for (int rt = 0; rt < NT; ++rt)
+                        for (int m = 0; m < NMAT; ++m)
 #pragma unroll
-                            for (int m = 0; m < NMAT; ++m)
-#pragma unroll
-                                for (int v = 0; v < 4; ++v) {
-                                    const int c = c0 + cc;
-                                    const bool live = c < nct && rt * 16 + grp * 4 + v < M;
-                                    x[cc][rt][m][v] =
-                                        live ? ld_f32<true>(all + (((size_t)c * NT + rt) * NMAT + m) * 256 + (grp * 4 + v) * 16 + jj)
-                                             : 0.f;
-                                    miss |= live && __float_as_uint(x[cc][rt][m][v]) == kSentinel;
-                                }
+                            for (int v = 0; v < 4; ++v) {
+                                const int c = c0 + cc;
+                                const bool live = c < nct && grp * 4 + v < M;
+                                x[cc][m][v] = live ? ld_f32<true>(all + ((size_t)c * NMAT + m) * 256 + (grp * 4 + v) * 16 + jj)
+                                                   : 0.f;
+                                miss |= live && __float_as_uint(x[cc][m][v]) == kSentinel;
+                            }
                     if (!__ballot(miss) || poll_abort(n, p.err)) break;
                     __builtin_amdgcn_s_sleep(1);
                 }
@@ -407,47 +350,34 @@ __global__ void __launch_bounds__(kSkWaves * 64) __attribute__((amdgpu_waves_per
                     const int c = c0 + cc;
                     if (c >= nct) break;
 #pragma unroll
-                    for (int rt = 0; rt < NT; ++rt)
+                    for (int m = 0; m < NMAT; ++m)
 #pragma unroll
-                        for (int m = 0; m < NMAT; ++m)
-#pragma unroll
-                            for (int v = 0; v < 4; ++v) {
-                                acc[rt][m][v] += x[cc][rt][m][v];
-                                if (rt * 16 + grp * 4 + v < M)
-                                    st_f32<true>(all + (((size_t)c * NT + rt) * NMAT + m) * 256 + (grp * 4 + v) * 16 + jj,
-                                                 __uint_as_float(kSentinel));
-                            }
+                        for (int v = 0; v < 4; ++v) {
+                            acc[m][v] += x[cc][m][v];
+                            if (grp * 4 + v < M)
+                                st_f32<true>(all + ((size_t)c * NMAT + m) * 256 + (grp * 4 + v) * 16 + jj,
+                                             __uint_as_float(kSentinel));
+                        }
                 }
             }
         }
         finish(t, acc);
     };
-    u32x4 B0[S][NMAT], B1[S][NMAT], A0[S][NT], A1[S][NT];
+    u32x4 B0[S][NMAT], B1[S][NMAT], A0[S], A1[S];
     long long u = u0;
     int n0 = u < u1 ? round_len(u) : 0, n1 = 0;
-    auto mfma_round = [&](const u32x4 (&A)[S][NT], const u32x4 (&B)[S][NMAT]) {
+    auto mfma_round = [&](const u32x4 (&A)[S], const u32x4 (&B)[S][NMAT]) {
 #pragma unroll
-        for (int i = 0; i < S; ++i)
-#pragma unroll
-            for (int rt = 0; rt < NT; ++rt)
-                if (rt < ntl) mfma_step<WT, NMAT>(A[i][rt], B[i], acc[rt]);
+        for (int i = 0; i < S; ++i) mfma_step<WT, NMAT>(A[i], B[i], acc);
     };
     auto clear = [&]() {
 #pragma unroll
-        for (int rt = 0; rt < NT; ++rt)
-#pragma unroll
-            for (int k = 0; k < NMAT; ++k) acc[rt][k] = f32x4{0.f, 0.f, 0.f, 0.f};
+        for (int k = 0; k < NMAT; ++k) acc[k] = f32x4{0.f, 0.f, 0.f, 0.f};
     };
-    if (n0) sk_load<WT, NMAT, S, NT>(q, ns, u, n0, lane, M, ntl, B0, A0);
-    // 1/rms of the rows and (launches of more than 16 rows) the rows'
-    // epilogue fields, shared by the workgroup's waves, while the first round
+    if (n0) sk_load<WT, NMAT, S>(q, ns, u, n0, lane, M, B0, A0);
+    // 1/rms of the rows, shared by the workgroup's waves, while the first round
     // is in flight (every wave reaches this barrier once)
     if (EPI != EPI_RESID) sk_rinv(p, M, wv, lane, rinv);
-    if (NT > 1 && (EPI == EPI_RESID || EPI == EPI_QKV))
-        for (int m = threadIdx.x; m < M; m += kSkWaves * 64) {
-            const Row& r = p.rows[m];
-            meta[m] = SkRowMeta{r.xrow, r.pos, r.slot, r.seq, r.depth};
-        }
     __syncthreads();
     while (n0) {
         // ---- round in B0 / A0 ------------------------------------------------
@@ -456,7 +386,7 @@ __global__ void __launch_bounds__(kSkWaves * 64) __attribute__((amdgpu_waves_per
         // issued even when no round follows (zeros from an empty range): the
         // MFMAs below then wait for exactly the loads issued before these, so
         // the next round stays in flight while they run
-        sk_load<WT, NMAT, S, NT>(q, ns, un, n1, lane, M, ntl, B1, A1);
+        sk_load<WT, NMAT, S>(q, ns, un, n1, lane, M, B1, A1);
         mfma_round(A0, B0);
         if (un % ns == 0 || un == u1) {
             flush(un);
@@ -467,7 +397,7 @@ __global__ void __launch_bounds__(kSkWaves * 64) __attribute__((amdgpu_waves_per
         // ---- round in B1 / A1 ------------------------------------------------
         un = u + n1;
         n0 = un < u1 ? round_len(un) : 0;
-        sk_load<WT, NMAT, S, NT>(q, ns, un, n0, lane, M, ntl, B0, A0);
+        sk_load<WT, NMAT, S>(q, ns, un, n0, lane, M, B0, A0);
         mfma_round(A1, B1);
         if (un % ns == 0 || un == u1) {
             flush(un);
@@ -477,45 +407,37 @@ __global__ void __launch_bounds__(kSkWaves * 64) __attribute__((amdgpu_waves_per
     }
 }
 
-// k steps per round.  16 rows: one workgroup per CU, so one wave per SIMD,
-// each with two rounds in flight (6 k steps of two matrices or 9 of one: 12
-// or 9 KB per round; measured against 4–18).  With several waves per SIMD the
-// arbiter serves the oldest first, so the waves of the workgroups placed
-// first on a CU end their (equal) ranges long before the last ones, and the
-// launch's tail runs on a fraction of the CU's requests; a single wave per
-// SIMD has no such skew.  32 and 64 rows: one workgroup per CU too, with
-// rounds sized for two waves per SIMD (the NT activation fragments per step
-// take the registers; the 64-row residual variant also holds its epilogue
-// operands of four row tiles).
-template <int EPI, int NMAT, int NT>
+// k steps per round: one workgroup per CU, so one wave per SIMD, each with two
+// rounds in flight (6 k steps of two matrices or 9 of one: 12 or 9 KB per
+// round; measured against 4–18).  With several waves per SIMD the arbiter
+// serves the oldest first, so the waves of the workgroups placed first on a CU
+// end their (equal) ranges long before the last ones, and the launch's tail
+// runs on a fraction of the CU's requests; a single wave per SIMD has no such
+// skew.
+template <int NMAT>
 constexpr int sk_steps() {
-    return NT == 1 ? (NMAT == 2 ? 6 : 9) : EPI == EPI_RESID && NT == 4 ? 2 : 16 / (NMAT + NT);
+    return NMAT == 2 ? 6 : 9;
 }
 
 template <typename WT, int EPI, int NMAT>
-static const void* sk_fn(int nt) {
-    switch (nt) {
-        case 1: return (const void*)k_gemm_sk<WT, EPI, NMAT, sk_steps<EPI, NMAT, 1>(), 1>;
-        case 2: return (const void*)k_gemm_sk<WT, EPI, NMAT, sk_steps<EPI, NMAT, 2>(), 2>;
-        case 4: return (const void*)k_gemm_sk<WT, EPI, NMAT, sk_steps<EPI, NMAT, 4>(), 4>;
-    }
-    return nullptr;
+static const void* sk_fn() {
+    return (const void*)k_gemm_sk<WT, EPI, NMAT, sk_steps<NMAT>()>;
 }
 
-static const void* sk_kernel(int epi, bool bf16, int nt) {
+static const void* sk_kernel(int epi, bool bf16) {
     if (bf16) {
         switch (epi) {
-            case EPI_QKV: return sk_fn<uint16_t, EPI_QKV, 1>(nt);
-            case EPI_RESID: return sk_fn<uint16_t, EPI_RESID, 1>(nt);
-            case EPI_SWIGLU: return sk_fn<uint16_t, EPI_SWIGLU, 2>(nt);
-            case EPI_LOGITS: return sk_fn<uint16_t, EPI_LOGITS, 1>(nt);
+            case EPI_QKV: return sk_fn<uint16_t, EPI_QKV, 1>();
+            case EPI_RESID: return sk_fn<uint16_t, EPI_RESID, 1>();
+            case EPI_SWIGLU: return sk_fn<uint16_t, EPI_SWIGLU, 2>();
+            case EPI_LOGITS: return sk_fn<uint16_t, EPI_LOGITS, 1>();
         }
     } else {
         switch (epi) {
-            case EPI_QKV: return sk_fn<float, EPI_QKV, 1>(nt);
-            case EPI_RESID: return sk_fn<float, EPI_RESID, 1>(nt);
-            case EPI_SWIGLU: return sk_fn<float, EPI_SWIGLU, 2>(nt);
-            case EPI_LOGITS: return sk_fn<float, EPI_LOGITS, 1>(nt);
+            case EPI_QKV: return sk_fn<float, EPI_QKV, 1>();
+            case EPI_RESID: return sk_fn<float, EPI_RESID, 1>();
+            case EPI_SWIGLU: return sk_fn<float, EPI_SWIGLU, 2>();
+            case EPI_LOGITS: return sk_fn<float, EPI_LOGITS, 1>();
         }
     }
     return nullptr;
@@ -525,10 +447,10 @@ static const void* sk_kernel(int epi, bool bf16, int nt) {
 // least one k step per wave.  *grid = 0 when the launch has fewer k steps
 // than a workgroup has waves (the tiled direct path runs it instead).
 // *contrib: the most waves a tile's stream can be split over (partial slots).
-hipError_t gemm_sk_shape(int epi, bool bf16, int nt, int tiles, int K, int* grid, int* contrib) {
+hipError_t gemm_sk_shape(int epi, bool bf16, int tiles, int K, int* grid, int* contrib) {
     *grid = 0;
     *contrib = 0;
-    const void* f = sk_kernel(epi, bf16, nt);
+    const void* f = sk_kernel(epi, bf16);
     if (!f) return hipErrorInvalidValue;
     int dev = 0, cus = 0, per = 0;
     hipError_t e;
@@ -540,7 +462,7 @@ hipError_t gemm_sk_shape(int epi, bool bf16, int nt, int tiles, int K, int* grid
     // every workgroup resident, and at least kSkMinSteps k steps per wave (a
     // shorter share spends more on its tile's fix-up than on its stream)
     long long G = (long long)cus * std::max(per, 1);
-    G = std::min(G, U / (kSkWaves * (nt == 1 ? kSkMinSteps : kSkMinStepsWide)));
+    G = std::min(G, U / (kSkWaves * kSkMinSteps));
     if (G < 1) G = U / kSkWaves;
     if (G < 1) return hipSuccess;          // too few k steps to give every wave one: not used
     const long long P = G * kSkWaves, minw = U / P;
@@ -549,8 +471,8 @@ hipError_t gemm_sk_shape(int epi, bool bf16, int nt, int tiles, int K, int* grid
     return hipSuccess;
 }
 
-hipError_t launch_gemm_sk(const GemmParams& p, int epi, bool bf16, int nt, int grid, hipStream_t st) {
-    const void* f = sk_kernel(epi, bf16, nt);
+hipError_t launch_gemm_sk(const GemmParams& p, int epi, bool bf16, int grid, hipStream_t st) {
+    const void* f = sk_kernel(epi, bf16);
     if (!f || grid < 1) return hipErrorInvalidValue;
     GemmParams q = p;
     void* args[] = {(void*)&q};

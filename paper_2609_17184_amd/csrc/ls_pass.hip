@@ -319,7 +319,7 @@ static size_t pass_lds_gemm(const PassParams& pp, int wbytes) {
     const GemmParams* g[4] = {&pp.qkv, &pp.o, &pp.gu, &pp.down};
     const int epi[4] = {EPI_QKV, EPI_RESID, EPI_SWIGLU, EPI_RESID};
     for (int k = 0; k < 4; ++k)
-        m = std::max(m, gemm_lds_bytes(wbytes, epi[k], epi[k] == EPI_SWIGLU ? 2 : 1, g[k]->tpw, g[k]->ks, 32, 1));
+        m = std::max(m, gemm_lds_bytes(epi[k] == EPI_SWIGLU ? 2 : 1, g[k]->tpw, g[k]->ks, 1));
     if (pp.attn_wg) m = std::max(m, attention_lds_bytes(pp.attn.chunks_cap, pp.attn.g.dh));
     return (m + 15) & ~(size_t)15;
 }

@@ -6,14 +6,6 @@ namespace ls {
 
 constexpr int kPrefillRowsMax = 2048;   // prompt rows one prefill pass carries (buffers of a handle are sized for it)
 
-// Prompt activations are stored in MFMA operand order: fragments of 16 rows x
-// one k step (32 fp16 or 16 fp32 columns) of 1 KB, row tile by row tile, lane
-// l of a fragment holding 16 bytes of row l % 16.  Element (m, k), k in VEC groups:
-template <typename WT>
-__device__ __forceinline__ size_t prefill_elem(int m, int k, int K) {
-    constexpr int VEC = 16 / sizeof(WT), KSTEP = 4 * VEC;
-    return ((size_t)(m / 16) * (K / KSTEP) + k / KSTEP) * (64 * VEC) + ((k % KSTEP) / VEC * 16 + m % 16) * VEC + k % VEC;
-}
 // The fp32 state of prompt rows: [row tile][group of 4 columns][16 rows][4]; element (m, k), k a multiple of 4
 __device__ __forceinline__ size_t prefill_state(int m, int k, int h) {
     return ((size_t)(m / 16) * (h / 4) + k / 4) * 64 + (m % 16) * 4;

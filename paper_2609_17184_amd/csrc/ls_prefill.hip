@@ -8,7 +8,7 @@
 // Both operands lie in memory in MFMA operand order (fragments of 16 rows x
 // one k step, a lane's 16 bytes at lane * 16): the weights packed when they are
 // bound, the activations because every prompt kernel writes them that way
-// (prefill_elem).  A wave's load is 1 KB of consecutive bytes: in row-major
+// (opd_elem).  A wave's load is 1 KB of consecutive bytes: in row-major
 // order the 16 rows of a fragment lie a multiple of 4 KB apart (K = 2048), on
 // one L2 channel.  The product is formed transposed (weights as the MFMA's A operand): a lane ends with four
 // consecutive features of one row.  Partials meet in
@@ -38,39 +38,9 @@
 
 #include <algorithm>
 
-#include "ls_gemm_dev.h"
+#include "ls_opd_dev.h"
 
 namespace ls {
-
-// acc += (16 x k)(k x 16) of one k step (KSTEP values of k), x the A operand
-template <typename WT>
-__device__ __forceinline__ void mfma_one(const u32x4& x, const u32x4& y, f32x4& acc) {
-    if constexpr (sizeof(WT) == 2) {
-        acc = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(f16x8, x), __builtin_bit_cast(f16x8, y), acc, 0,
-                                                     0, 0);
-    } else {
-        const f32x4 a = __builtin_bit_cast(f32x4, x), b = __builtin_bit_cast(f32x4, y);
-#pragma unroll
-        for (int e = 0; e < 4; ++e) acc = __builtin_amdgcn_mfma_f32_16x16x4f32(a[e], b[e], acc, 0, 0, 0);
-    }
-}
-
-// eight (fp16) or four (fp32) consecutive values in the compute dtype: 16 bytes
-template <typename WT>
-__device__ __forceinline__ u32x4 pack16(const float* v) {
-    if constexpr (sizeof(WT) == 2)
-        return u32x4{pack_h2(v[0], v[1]), pack_h2(v[2], v[3]), pack_h2(v[4], v[5]), pack_h2(v[6], v[7])};
-    else
-        return __builtin_bit_cast(u32x4, f32x4{v[0], v[1], v[2], v[3]});
-}
-
-// Values k .. k + 15 of row m (k a multiple of 16) into an activation buffer of K columns
-template <typename WT>
-__device__ __forceinline__ void store_act16(void* base, int m, int k, int K, const float* v) {
-    constexpr int VEC = WTraits<WT>::VEC;
-#pragma unroll
-    for (int e = 0; e < 16; e += VEC) *(u32x4*)((WT*)base + prefill_elem<WT>(m, k + e, K)) = pack16<WT>(v + e);
-}
 
 // The workgroup's tile from NP partials in LDS ([NP][BM][NMAT * BN + 4] fp32,
 // summed in order) through the epilogue of its kind: BM rows from m0, feature
@@ -569,7 +539,7 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) k
         if (m >= p.M) continue;
 #pragma unroll
         for (int t = 0; t < DT; ++t)
-            *(uint2*)((uint16_t*)p.out + prefill_elem<uint16_t>(m, head * DH + t * 16 + grp * 4, p.g.h)) =
+            *(uint2*)((uint16_t*)p.out + opd_elem<uint16_t>(m, head * DH + t * 16 + grp * 4, p.g.h)) =
                 make_uint2(pack_h2(o[n][t][0] * r, o[n][t][1] * r), pack_h2(o[n][t][2] * r, o[n][t][3] * r));
     }
 }

@@ -34,14 +34,12 @@ namespace {
 
 constexpr size_t kLdsBudget = 80 * 1024;     // preferred GEMM workgroup LDS (two workgroups per CU)
 constexpr size_t kLdsMax = 160 * 1024;       // LDS of one CU: the hard limit of a workgroup
-constexpr size_t kSkWideBytes = 64u << 20;   // weight bytes from which launches of 17..64 rows run stream-K
 
 struct GemmCfg {
-    int ks = 1, tpw = 1, kc = 32, kg = 1;
+    int ks = 1, tpw = 1, kg = 1;
     bool ok = true;
-    // stream-K launches of 16, 32 and 64 rows (index 0, 1, 2): grid and
-    // partial slots per tile (grid 0: that width takes the tiled GEMM)
-    int sk_grid[3] = {0, 0, 0}, sk_c[3] = {0, 0, 0};
+    // stream-K launch: grid and partial slots per tile (grid 0: the direct path)
+    int sk_grid = 0, sk_c = 0;
 };
 
 // Direct-path launch shape targets: about 16 waves per CU over the chip, and
@@ -142,8 +140,8 @@ struct loopspec_handle {
     std::vector<PackedLayer> packed;   // MFMA-order copies (owned, in `folded`)
     const void* head_packed = nullptr;
 
-    // gemm configs: [0] direct path (<= 16 rows), [1] 64-row path (decode with more than 16 slots)
-    GemmCfg cfg_qkv[2], cfg_o[2], cfg_gu[2], cfg_down[2], cfg_head[2];
+    // launches of at most 16 rows (those of more need no configuration)
+    GemmCfg cfg_qkv, cfg_o, cfg_gu, cfg_down, cfg_head;
     float* gpart = nullptr;       // split-k partials of the direct path
     unsigned* gcnt = nullptr;     // split-k arrival counters (one per tile, zero between launches)
 
@@ -229,48 +227,29 @@ int dalloc(loopspec_t h, T** p, size_t n) {
     return LOOPSPEC_OK;
 }
 
-// Launch configuration of the standalone GEMM.  nt_max = 1: the direct path
-// (at most 16 rows), where each wave holds all of its k steps in registers,
-// at most gemm_max_steps(epi, 1) of them: k is cut into ks * kg contiguous
-// slices, ks per workgroup and kg workgroups per tile.  nt_max > 1: the
-// 64-row path, which streams k in rounds.  c.ok = false when no split fits.
-GemmCfg pick_cfg(const loopspec_t h, int tiles, int K, int nmat, int epi, int nt_max) {
+// Launch configuration of the direct path (at most 16 rows), where each wave
+// holds all of its k steps in registers, at most gemm_max_steps(epi) of them:
+// k is cut into ks * kg contiguous slices, ks per workgroup and kg workgroups
+// per tile.  c.ok = false when no split fits.
+GemmCfg pick_cfg(const loopspec_t h, int tiles, int K, int nmat, int epi) {
     GemmCfg c;
-    const int kstep = h->bf16 ? 32 : 16;
-    const int nsteps = K / kstep;
-    const int vec = h->bf16 ? 8 : 4;
-    if (nt_max <= 1) {
-        const int per = gemm_max_steps(epi, 1);
-        int KS = (nsteps + per - 1) / per;             // fewest slices whose shares fit
-        const int want = (kWaveTarget + tiles - 1) / tiles;
-        KS = std::max(KS, std::min(want, nsteps / 3)); // thin launches: more slices, >= 3 steps each
-        int kg = (KS + 15) / 16;
-        kg = std::max(kg, std::min(KS, (kWgTarget + tiles - 1) / tiles));
-        kg = std::min(kg, 16);
-        c.kg = kg;
-        c.ks = (KS + kg - 1) / kg;
-        if (c.ks > 16) c.ok = false;
-        const int KSt = c.ks * c.kg;
-        if ((nsteps + KSt - 1) / KSt > per) c.ok = false;
-        if (c.kg == 1)
-            while (c.tpw * c.ks < 8 && tiles / (c.tpw * 2) >= 512) c.tpw *= 2;
-        c.kc = kstep;
-        while (gemm_lds_bytes(h->wbytes, epi, nmat, c.tpw, c.ks, c.kc, 1, c.kg) > kLdsBudget && c.tpw > 1) c.tpw /= 2;
-        if (gemm_lds_bytes(h->wbytes, epi, nmat, c.tpw, c.ks, c.kc, 1, c.kg) > kLdsMax) c.ok = false;
-        return c;
-    }
-    // 64-row path: each wave streams its steps (every ks-th) in rounds
-    const int per = gemm_max_steps(epi, 4);
-    c.ks = std::min(16, std::max(1, (nsteps + per - 1) / per));
-    // more slices while the launch has few waves (latency hiding), up to 16 per workgroup
-    while (c.ks * 2 <= 16 && tiles * c.ks < 2048 && nsteps / (c.ks * 2) >= 2) c.ks *= 2;
-    while (c.tpw * c.ks < 8 && tiles / (c.tpw * 2) >= 512) c.tpw *= 2;
-    // LDS k chunk: the activation tile of nt_max*16 rows must fit the budget
-    int kc = (int)(kLdsBudget - 256) / (nt_max * 16 * h->wbytes) - vec;
-    kc = std::max(kstep, kc / kstep * kstep);
-    c.kc = std::min(kc, K);
-    while (gemm_lds_bytes(h->wbytes, epi, nmat, c.tpw, c.ks, c.kc, nt_max) > kLdsBudget && c.tpw > 1) c.tpw /= 2;
-    if (gemm_lds_bytes(h->wbytes, epi, nmat, c.tpw, c.ks, c.kc, nt_max) > kLdsMax) c.ok = false;
+    const int nsteps = K / (h->bf16 ? 32 : 16);
+    const int per = gemm_max_steps(epi);
+    int KS = (nsteps + per - 1) / per;             // fewest slices whose shares fit
+    const int want = (kWaveTarget + tiles - 1) / tiles;
+    KS = std::max(KS, std::min(want, nsteps / 3)); // thin launches: more slices, >= 3 steps each
+    int kg = (KS + 15) / 16;
+    kg = std::max(kg, std::min(KS, (kWgTarget + tiles - 1) / tiles));
+    kg = std::min(kg, 16);
+    c.kg = kg;
+    c.ks = (KS + kg - 1) / kg;
+    if (c.ks > 16) c.ok = false;
+    const int KSt = c.ks * c.kg;
+    if ((nsteps + KSt - 1) / KSt > per) c.ok = false;
+    if (c.kg == 1)
+        while (c.tpw * c.ks < 8 && tiles / (c.tpw * 2) >= 512) c.tpw *= 2;
+    while (gemm_lds_bytes(nmat, c.tpw, c.ks, c.kg) > kLdsBudget && c.tpw > 1) c.tpw /= 2;
+    if (gemm_lds_bytes(nmat, c.tpw, c.ks, c.kg) > kLdsMax) c.ok = false;
     return c;
 }
 
@@ -287,7 +266,6 @@ bool pick_pass_cfg(const loopspec_t h, int tiles, int K, int kind, int grid, Gem
         if (it <= grid && (nsteps + ks - 1) / ks <= pass_max_steps(kind, h->g.h > 2048)) {
             c->tpw = tpw;
             c->ks = ks;
-            c->kc = 32;
             *items = it;
             found = true;
             if (kind != PK_O) break;
@@ -313,19 +291,17 @@ GemmParams gemm_base(loopspec_t h, const Row* rows, const int32_t* nrows) {
     return p;
 }
 
-hipError_t run_gemm(loopspec_t h, GemmParams p, int epi, const GemmCfg& c, int nt_max) {
-    const int si = nt_max <= 1 ? 0 : nt_max <= 2 ? 1 : nt_max <= 4 ? 2 : -1;
-    if (si >= 0 && c.sk_grid[si] > 0) {
-        p.kg = c.sk_c[si];
+hipError_t run_gemm(loopspec_t h, GemmParams p, int epi, const GemmCfg& c, int rows_cap) {
+    if (rows_cap > 16) return launch_gemm_rows(p, epi, h->bf16, rows_cap, h->st);
+    if (c.sk_grid > 0) {
+        p.kg = c.sk_c;
         p.part = h->skpart;
-        if (!p.err) p.err = h->sch.err;
-        return launch_gemm_sk(p, epi, h->bf16, 1 << si, c.sk_grid[si], h->st);
+        return launch_gemm_sk(p, epi, h->bf16, c.sk_grid, h->st);
     }
     p.ks = c.ks;
     p.tpw = c.tpw;
-    p.kc = c.kc;
-    p.kg = nt_max <= 1 ? c.kg : 1;
-    return launch_gemm(p, epi, h->bf16, nt_max, h->st);
+    p.kg = c.kg;
+    return launch_gemm(p, epi, h->bf16, h->st);
 }
 
 // One launch of kernel `k` (0 QKV, 1 attention, 2 O, 3 gate/up, 4 down) of
@@ -333,10 +309,8 @@ hipError_t run_gemm(loopspec_t h, GemmParams p, int epi, const GemmCfg& c, int n
 // keys and values all are in the committed cache (a prompt's last position).
 hipError_t enqueue_kernel_(loopspec_t h, int k, int stack, int l, const Row* rows, const int32_t* nrows,
                            int rows_cap, bool committed) {
-    const int nt_max = (rows_cap + 15) / 16;
     const int first = stack == STACK_PRE ? 0 : stack == STACK_CORE ? h->g.Lp : h->g.Lp + h->g.Lb;
     const int hd = h->g.h, F = h->g.F;
-    const int b = nt_max > 1 ? 1 : 0;            // direct path (<= 16 rows) or 64-row path
     const loopspec_handle::PackedLayer& w = h->packed[first + l];
     hipError_t e = hipSuccess;
     switch (k) {
@@ -352,7 +326,7 @@ hipError_t enqueue_kernel_(loopspec_t h, int k, int stack, int l, const Row* row
             p.rope = h->rope;
             p.stack = stack;
             p.layer = l;
-            return run_gemm(h, p, EPI_QKV, h->cfg_qkv[b], nt_max);
+            return run_gemm(h, p, EPI_QKV, h->cfg_qkv, rows_cap);
         }
         case 1: {   // attention at each row's own depth
             AttnParams a{};
@@ -366,6 +340,7 @@ hipError_t enqueue_kernel_(loopspec_t h, int k, int stack, int l, const Row* row
             a.layer = l;
             a.chunks_cap = h->chunks_cap;
             a.out = h->att;
+            a.opd = rows_cap > 16;
             const bool tasks = !committed && h->attn_part;
             return launch_attention(a, h->bf16, rows_cap, tasks ? h->attn_part : nullptr, tasks ? h->attn_cnt : nullptr,
                                     h->st);
@@ -377,7 +352,7 @@ hipError_t enqueue_kernel_(loopspec_t h, int k, int stack, int l, const Row* row
             p.Wp = w.o;
             p.N_mat = hd;
             p.tiles = hd / kTile;
-            return run_gemm(h, p, EPI_RESID, h->cfg_o[b], nt_max);
+            return run_gemm(h, p, EPI_RESID, h->cfg_o, rows_cap);
         }
         case 3: {   // RMSNorm + gate/up + SwiGLU
             GemmParams p = gemm_base(h, rows, nrows);
@@ -386,7 +361,7 @@ hipError_t enqueue_kernel_(loopspec_t h, int k, int stack, int l, const Row* row
             p.N_mat = F;
             p.tiles = F / kTile;
             p.act = h->act;
-            return run_gemm(h, p, EPI_SWIGLU, h->cfg_gu[b], nt_max);
+            return run_gemm(h, p, EPI_SWIGLU, h->cfg_gu, rows_cap);
         }
         case 4: {   // down projection + residual
             GemmParams p = gemm_base(h, rows, nrows);
@@ -395,7 +370,7 @@ hipError_t enqueue_kernel_(loopspec_t h, int k, int stack, int l, const Row* row
             p.Wp = w.down;
             p.N_mat = hd;
             p.tiles = hd / kTile;
-            return run_gemm(h, p, EPI_RESID, h->cfg_down[b], nt_max);
+            return run_gemm(h, p, EPI_RESID, h->cfg_down, rows_cap);
         }
     }
     return e;
@@ -419,7 +394,6 @@ PassParams pass_params(loopspec_t h, int stack, const Row* rows, const int32_t* 
         *kinds[k] = gemm_base(h, rows, nrows);
         kinds[k]->tpw = h->pcfg[k].tpw;
         kinds[k]->ks = h->pcfg[k].ks;
-        kinds[k]->kc = h->pcfg[k].kc;
     }
     pp.qkv.K = hd;
     pp.qkv.N_mat = hd;
@@ -481,7 +455,7 @@ hipError_t enqueue_stack(loopspec_t h, int stack, const Row* rows, const int32_t
         prof_done(h, armed);
         return e;
     }
-    if ((e = launch_gather(h->g, rows, nrows, rows_cap, h->X, h->pb, h->bf16, h->st)) != hipSuccess) return e;
+    if ((e = launch_gather(h->g, rows, nrows, rows_cap, h->X, h->pb, h->bf16, rows_cap > 16, h->st)) != hipSuccess) return e;
     for (int l = 0; l < n; ++l)
         for (int k = 0; k < 5; ++k) {
             e = enqueue_kernel(h, k, stack, l, rows, nrows, rows_cap, false);
@@ -491,7 +465,7 @@ hipError_t enqueue_stack(loopspec_t h, int stack, const Row* rows, const int32_t
 }
 
 hipError_t enqueue_head(loopspec_t h, const Row* rows, const int32_t* nrows, int rows_cap) {
-    hipError_t e = launch_gather(h->g, rows, nrows, rows_cap, h->X, h->pb, h->bf16, h->st);
+    hipError_t e = launch_gather(h->g, rows, nrows, rows_cap, h->X, h->pb, h->bf16, rows_cap > 16, h->st);
     if (e != hipSuccess) return e;
     GemmParams p = gemm_base(h, rows, nrows);
     p.K = h->g.h;
@@ -501,9 +475,8 @@ hipError_t enqueue_head(loopspec_t h, const Row* rows, const int32_t* nrows, int
     p.logits = h->logits;
     p.tmax = h->tmax;
     p.targ = h->targ;
-    const int nt_max = (rows_cap + 15) / 16;
     const bool armed = prof_arm(h, h->prof_kind == LOOPSPEC_PROF_HEAD);
-    e = run_gemm(h, p, EPI_LOGITS, h->cfg_head[nt_max > 1 ? 1 : 0], nt_max);
+    e = run_gemm(h, p, EPI_LOGITS, h->cfg_head, rows_cap);
     prof_done(h, armed);
     return e;
 }
@@ -823,36 +796,26 @@ int loopspec_create(const loopspec_dims* dims, const loopspec_config* cfg, void*
         HIPCHK(h, hipMemcpy(h->rope, t.data(), t.size() * 4, hipMemcpyHostToDevice));
     }
 
-    // launch configurations: the direct path (rows <= 16) and the 64-row path
-    // (decode with more than 16 slots)
+    // launch configurations of at most 16 rows: stream-K, the direct path where
+    // a launch is too small for it
     {
         size_t part_elems = 0, sk_elems = 0;
         int cnt_n = 0;
-        for (int b = 0; b < 2; ++b) {
-            const int nt = b ? (kMaxRows + 15) / 16 : 1;
-            struct K { GemmCfg* c; int tiles, K, nmat, epi; } ks[] = {
-                {&h->cfg_qkv[b], 3 * g.h / 16, g.h, 1, EPI_QKV}, {&h->cfg_o[b], g.h / 16, g.h, 1, EPI_RESID},
-                {&h->cfg_gu[b], g.F / 16, g.h, 2, EPI_SWIGLU}, {&h->cfg_down[b], g.h / 16, g.F, 1, EPI_RESID},
-                {&h->cfg_head[b], (int)tiles, g.h, 1, EPI_LOGITS}};
-            for (const K& k : ks) {
-                *k.c = pick_cfg(h, k.tiles, k.K, k.nmat, k.epi, nt);
-                if (!k.c->ok)
-                    return fail(h, LOOPSPEC_EINVAL, "no GEMM launch configuration fits K = " + std::to_string(k.K) +
-                                                        " (registers of one wave, LDS of one CU)");
-                if (k.c->kg > 1) {
-                    part_elems = std::max(part_elems, (size_t)k.tiles * k.c->kg * k.nmat * 256);
-                    cnt_n = std::max(cnt_n, k.tiles);
-                }
-                // launches of at most 16 rows stream the weights stream-K; wider
-                // ones too when the launch streams at least kSkWideBytes (below
-                // that, the stream-K fix-up and per-launch set-up cost more than
-                // the 64-row tiles lose)
-                const bool wide_sk = (size_t)k.tiles * 16 * k.K * h->wbytes * k.nmat >= kSkWideBytes;
-                for (int si = b ? 1 : 0; si < (b ? (wide_sk ? 3 : 1) : 1); ++si) {
-                    HIPCHK(h, gemm_sk_shape(k.epi, h->bf16, 1 << si, k.tiles, k.K, &k.c->sk_grid[si], &k.c->sk_c[si]));
-                    sk_elems = std::max(sk_elems, (size_t)k.tiles * k.c->sk_c[si] * k.nmat * 256 * (1 << si));
-                }
+        struct K { GemmCfg* c; int tiles, K, nmat, epi; } ks[] = {
+            {&h->cfg_qkv, 3 * g.h / 16, g.h, 1, EPI_QKV}, {&h->cfg_o, g.h / 16, g.h, 1, EPI_RESID},
+            {&h->cfg_gu, g.F / 16, g.h, 2, EPI_SWIGLU}, {&h->cfg_down, g.h / 16, g.F, 1, EPI_RESID},
+            {&h->cfg_head, (int)tiles, g.h, 1, EPI_LOGITS}};
+        for (const K& k : ks) {
+            *k.c = pick_cfg(h, k.tiles, k.K, k.nmat, k.epi);
+            if (!k.c->ok)
+                return fail(h, LOOPSPEC_EINVAL, "no GEMM launch configuration fits K = " + std::to_string(k.K) +
+                                                    " (registers of one wave, LDS of one CU)");
+            if (k.c->kg > 1) {
+                part_elems = std::max(part_elems, (size_t)k.tiles * k.c->kg * k.nmat * 256);
+                cnt_n = std::max(cnt_n, k.tiles);
             }
+            HIPCHK(h, gemm_sk_shape(k.epi, h->bf16, k.tiles, k.K, &k.c->sk_grid, &k.c->sk_c));
+            sk_elems = std::max(sk_elems, (size_t)k.tiles * k.c->sk_c * k.nmat * 256);
         }
         if ((r = dalloc(h, &h->gpart, std::max<size_t>(part_elems, 1)))) return r;
         // stream-K hand-over slots hold the sentinel between launches
@@ -1058,6 +1021,7 @@ hipError_t enqueue_prompt_block(loopspec_t h, int stack, int l, int depth, int s
         a.layer = l;
         a.chunks_cap = h->chunks_cap;
         a.out = h->att;
+        a.opd = 1;
         e = launch_attention_prompt(a, seq, p0, depth, m, h->st);
     }
     if (e != hipSuccess) return e;
@@ -1153,7 +1117,7 @@ int loopspec_prefill(loopspec_t h, int32_t seq, const int32_t* ids, int32_t n, i
     const int stack = Lc ? STACK_CODA : STACK_CORE;
     e = launch_prefill_row(h->g, h->X + (size_t)(Lc > 1 ? h->xrow_pf_coda : h->xrow_pf) * h->g.h, m_last - 1,
                            h->X + (size_t)h->xrow_last * h->g.h, h->st);
-    if (e == hipSuccess) e = launch_gather(h->g, h->pf_last, h->pf_one, 1, h->X, h->pb, h->bf16, h->st);
+    if (e == hipSuccess) e = launch_gather(h->g, h->pf_last, h->pf_one, 1, h->X, h->pb, h->bf16, false, h->st);
     for (int k = 0; k < 5 && e == hipSuccess; ++k)
         e = enqueue_kernel(h, k, stack, (Lc ? Lc : h->g.Lb) - 1, h->pf_last, h->pf_one, 1, true);
     if (e == hipSuccess) e = enqueue_head(h, h->pf_last, h->pf_one, 1);
@@ -1705,7 +1669,7 @@ int loopspec_time_kernels(loopspec_t h, int32_t M, int32_t reps, float* ms_out) 
     for (auto& e : ev) HIPCHK(h, hipEventCreate(&e));
     size_t n = 0;
     {
-        hipError_t e = launch_gather(h->g, h->pf_rows, h->pf_n, M, h->X, h->pb, h->bf16, h->st);
+        hipError_t e = launch_gather(h->g, h->pf_rows, h->pf_n, M, h->X, h->pb, h->bf16, h->S > 16, h->st);
         if (e != hipSuccess) return fail(h, LOOPSPEC_EHIP, hipGetErrorString(e));
     }
     HIPCHK(h, hipEventRecord(ev[n++], h->st));
@@ -1758,7 +1722,7 @@ int loopspec_time_pass(loopspec_t h, int32_t M, int32_t reps, float* ms_out, int
     for (auto& e : ev) HIPCHK(h, hipEventCreate(&e));
     for (int r = 0; r < reps; ++r) {
         hipError_t e = fused ? launch_pass_prep(pp, h->bf16, M, h->st)
-                             : launch_gather(h->g, h->pf_rows, h->pf_n, M, h->X, h->pb, h->bf16, h->st);
+                             : launch_gather(h->g, h->pf_rows, h->pf_n, M, h->X, h->pb, h->bf16, h->S > 16, h->st);
         if (e != hipSuccess) return fail(h, LOOPSPEC_EHIP, hipGetErrorString(e));
         HIPCHK(h, hipEventRecord(ev[2 * r], h->st));
         if (fused) {

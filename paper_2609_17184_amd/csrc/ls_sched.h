@@ -73,8 +73,8 @@ hipError_t launch_commit_embed(const Sched& s, void* kvc, const void* kvs, int w
 // X[row.xrow] = X[row.src] for every row (readout copies that coda blocks transform)
 hipError_t launch_copy_rows(const Geo& g, const Row* rows, const int32_t* nrows, int rows_cap, float* X,
                             hipStream_t st);
-// pass buffers of a row list: XB[m] = round(X[xrow]), SSQR[m] = per-tile sums of squares
+// pass buffers of a row list: XB[m] = round(X[xrow]) (opd: in operand order), SSQR[m] = per-tile sums of squares
 hipError_t launch_gather(const Geo& g, const Row* rows, const int32_t* nrows, int rows_cap, const float* X,
-                         PassBuf pb, bool bf16, hipStream_t st);
+                         PassBuf pb, bool bf16, bool opd, hipStream_t st);
 
 }  // namespace ls

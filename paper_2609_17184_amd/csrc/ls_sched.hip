@@ -390,7 +390,7 @@ hipError_t launch_embed(const Geo& g, const int32_t* jobs, const int32_t* njobs,
 // ---------------------------------------------------------------------------
 template <typename WT>
 __global__ void __launch_bounds__(256) k_gather(Geo g, const Row* rows, const int32_t* nrows, const float* X,
-                                                PassBuf pb) {
+                                                PassBuf pb, int opd) {
     const int m = blockIdx.x;
     if (m >= *nrows) return;
     const float* x = X + (size_t)rows[m].xrow * g.h;
@@ -401,20 +401,21 @@ __global__ void __launch_bounds__(256) k_gather(Geo g, const Row* rows, const in
         pb.SSQR[(size_t)m * g.ssq_tiles + t] = ssq16(v);
 #pragma unroll
         for (int c = 0; c < 16; ++c) {
+            const size_t i = opd ? opd_elem<WT>(m, t * 16 + c, g.h) : (size_t)m * g.h + t * 16 + c;
             if (sizeof(WT) == 2)
-                ((uint16_t*)pb.XB)[(size_t)m * g.h + t * 16 + c] = f2h(v[c]);
+                ((uint16_t*)pb.XB)[i] = f2h(v[c]);
             else
-                ((float*)pb.XB)[(size_t)m * g.h + t * 16 + c] = v[c];
+                ((float*)pb.XB)[i] = v[c];
         }
     }
 }
 
 hipError_t launch_gather(const Geo& g, const Row* rows, const int32_t* nrows, int rows_cap, const float* X,
-                         PassBuf pb, bool bf16, hipStream_t st) {
+                         PassBuf pb, bool bf16, bool opd, hipStream_t st) {
     if (bf16)
-        hipLaunchKernelGGL(k_gather<uint16_t>, dim3(rows_cap), dim3(128), 0, st, g, rows, nrows, X, pb);
+        hipLaunchKernelGGL(k_gather<uint16_t>, dim3(rows_cap), dim3(128), 0, st, g, rows, nrows, X, pb, (int)opd);
     else
-        hipLaunchKernelGGL(k_gather<float>, dim3(rows_cap), dim3(128), 0, st, g, rows, nrows, X, pb);
+        hipLaunchKernelGGL(k_gather<float>, dim3(rows_cap), dim3(128), 0, st, g, rows, nrows, X, pb, (int)opd);
     return hipGetLastError();
 }
 
