@@ -23,46 +23,77 @@
 namespace ls {
 
 // ---------------------------------------------------------------------------
-// scheduler (single thread: the tree holds at most 64 branches)
+// scheduler: one wave, lane x for slot x (the tree holds at most 64 branches)
+//
+// The bookkeeping is a chain of small dependent reads and writes, so what
+// bounds it is the latency of the tables: they come into LDS in one round trip
+// at the start (every load of the launch is issued before any is waited for)
+// and leave in one at the end.  The steps of Alg. 1 run in every lane alike (a
+// table entry that all lanes write gets the same value from each); what ranges
+// over slots -- pruning, free slots, the row lists of the next pass -- runs one
+// slot per lane.  With one thread on the tables in memory a step took 10 us
+// for one sequence and up to 73 us for a tree of 28 slots.
 // ---------------------------------------------------------------------------
-__device__ static int alloc_slot(const Sched& s) {
-    for (int i = 0; i < s.g.S; ++i)
-        if (!s.s_active[i]) return i;
-    return -1;
+static_assert(kMaxRows <= 64, "a slot per lane");
+
+struct SchedTree {
+    int active[64], seq[64], pos[64], tok[64], depth[64], parent[64], c1[64], c2[64], x1[64], x2[64], gate[64];
+    int root[64], tdone[64], ncommit[64], target[64], state[64], last_tok[64], last_src[64];
+    int r_slot[64], r_seq[64], r_pos[64], r_depth[64], ro_tok[64], ro_aux[64];   // readout rows of the step
+    int js[128];
+};
+
+// LDS written by some lanes is read by others after this
+__device__ __forceinline__ void lds_sync() { __syncthreads(); }
+
+__device__ __forceinline__ int alloc_slot(const SchedTree& t, int S, int lane) {
+    const unsigned long long m = __ballot(lane < S && !t.active[lane]);
+    return m ? (int)__builtin_ctzll(m) : -1;
 }
 
-__device__ static void init_slot(const Sched& s, int c, int q, int pos, int tok, int parent) {
-    s.s_active[c] = 1;
-    s.s_seq[c] = q;
-    s.s_pos[c] = pos;
-    s.s_tok[c] = tok;
-    s.s_depth[c] = 0;
-    s.s_parent[c] = parent;
-    s.s_c1[c] = -1;
-    s.s_c2[c] = -1;
-    s.s_x1[c] = -1;
-    s.s_x2[c] = -1;
-    s.s_gate[c] = 0;
+__device__ __forceinline__ void init_slot(SchedTree& t, int c, int q, int pos, int tok, int parent) {
+    t.active[c] = 1;
+    t.seq[c] = q;
+    t.pos[c] = pos;
+    t.tok[c] = tok;
+    t.depth[c] = 0;
+    t.parent[c] = parent;
+    t.c1[c] = -1;
+    t.c2[c] = -1;
+    t.x1[c] = -1;
+    t.x2[c] = -1;
+    t.gate[c] = 0;
+    lds_sync();
 }
 
-__device__ static bool in_subtree(const Sched& s, int x, int c) {
+__device__ __forceinline__ bool in_subtree(const SchedTree& t, int S, int x, int c) {
     if (c < 0) return false;
-    for (int k = 0; x >= 0 && k <= s.g.S; ++k) {
+    for (int k = 0; x >= 0 && k <= S; ++k) {
         if (x == c) return true;
-        x = s.s_parent[x];
+        x = t.parent[x];
     }
     return false;
 }
 
-__device__ static void fill_chain(const Sched& s, int slot, int tdone, Row& r) {
-    int x = s.s_parent[slot];
-    for (int p = s.s_pos[slot] - 1; p >= tdone; --p) {
-        if (p - tdone >= kChainMax || x < 0) {         // inconsistent tree: never index out of range
-            atomicOr(s.err, ERR_SLOTS);
+// Row of slot x at `depth` into *r
+__device__ __forceinline__ void put_row(const SchedTree& t, int x, int depth, int xrow, Row* r, int32_t* err) {
+    const int tdone = t.tdone[t.seq[x]], pos = t.pos[x];
+    r->xrow = xrow;
+    r->slot = x;
+    r->seq = t.seq[x];
+    r->pos = pos;
+    r->depth = depth;
+    r->tdone = tdone;
+    r->src = x;                                        // copy source for readout rows
+    r->pad = 0;
+    int y = t.parent[x];
+    for (int p = pos - 1; p >= tdone; --p) {
+        if (p - tdone >= kChainMax || y < 0) {         // inconsistent tree: never index out of range
+            atomicOr(err, ERR_SLOTS);
             break;
         }
-        r.anc[p - tdone] = x;
-        x = s.s_parent[x];
+        r->anc[p - tdone] = y;
+        y = t.parent[y];
     }
 }
 
@@ -72,139 +103,181 @@ __device__ static bool is_readout(const Sched& s, int mode, int d) {
     return d == s.d1 || (s.d2 > 0 && d == s.d2) || d == s.R;
 }
 
-__global__ void k_sched(Sched s, int op, int op_seq, int op_pos, const int32_t* op_tok) {
-    if (threadIdx.x != 0) return;
-    const int mode = *s.mode;
-    const int S = s.g.S, ctx = s.g.max_ctx;
-    long long* st = s.stats;
+__global__ void __launch_bounds__(64) k_sched(Sched s, int op, int op_seq, int op_pos, const int32_t* op_tok) {
+    __shared__ SchedTree t;
+    __shared__ long long st[ST_N];                     // what this step adds to the statistics
+    const int lane = threadIdx.x, S = s.g.S, Q = s.max_seqs, ctx = s.g.max_ctx;
+    // ---- the tables (rows past the lists' lengths are read and not used)
+    const int mode = *s.mode, nB0 = *s.nB, nC0 = *s.nC;
+    const int tok0 = op == OP_INIT ? op_tok[0] : -1;
+    int32_t* const slot_g[] = {s.s_active, s.s_seq, s.s_pos, s.s_tok, s.s_depth, s.s_parent,
+                               s.s_c1, s.s_c2, s.s_x1, s.s_x2, s.s_gate};
+    int* const slot_l[] = {t.active, t.seq, t.pos, t.tok, t.depth, t.parent, t.c1, t.c2, t.x1, t.x2, t.gate};
+    int32_t* const seq_g[] = {s.q_root, s.q_tdone, s.q_ncommit, s.q_target, s.q_state, s.q_last_tok, s.q_last_src};
+    int* const seq_l[] = {t.root, t.tdone, t.ncommit, t.target, t.state, t.last_tok, t.last_src};
+    int v[11], w[7], b_slot = 0, c[6] = {0, 0, 0, 0, 0, 0};
+    const bool has_slot = lane < S, has_seq = lane < Q;
+#pragma unroll
+    for (int i = 0; i < 11; ++i) v[i] = has_slot ? slot_g[i][lane] : 0;
+#pragma unroll
+    for (int i = 0; i < 7; ++i) w[i] = has_seq ? seq_g[i][lane] : 0;
+    if (op == OP_STEP && has_slot) {
+        b_slot = s.rowsB[lane].slot;
+        const Row& r = s.rowsC[lane];
+        c[0] = r.slot;
+        c[1] = r.seq;
+        c[2] = r.pos;
+        c[3] = r.depth;
+        c[4] = s.ro_tok[lane];
+        c[5] = s.ro_aux[lane];
+    }
+#pragma unroll
+    for (int i = 0; i < 11; ++i) slot_l[i][lane] = v[i];
+#pragma unroll
+    for (int i = 0; i < 7; ++i) seq_l[i][lane] = w[i];
+    t.r_slot[lane] = c[0];
+    t.r_seq[lane] = c[1];
+    t.r_pos[lane] = c[2];
+    t.r_depth[lane] = c[3];
+    t.ro_tok[lane] = c[4];
+    t.ro_aux[lane] = c[5];
+    for (int i = lane; i < ST_N; i += 64) st[i] = 0;
+    lds_sync();
     int njc = 0, njs = 0;
+    // (all lanes write the same values, so a statement's reads and writes need no order between lanes)
+    auto spawn = [&](int slot, int tok) {
+        t.js[2 * njs] = slot;
+        t.js[2 * njs + 1] = tok;
+        ++njs;
+    };
+    auto error = [&](int bit) {
+        if (lane == 0) atomicOr(s.err, bit);
+    };
+    // statistics: lane 0 keeps them
+    auto count = [&](int k, long long n) {
+        if (lane == 0) st[k] += n;
+    };
 
     if (op == OP_STEP) {
-        const int nB = *s.nB, nC = *s.nC;
-        for (int i = 0; i < nB; ++i) s.s_depth[s.rowsB[i].slot] += 1;
+        const int nB = min(nB0, S), nC = min(nC0, S);
+        if (lane < nB) t.depth[b_slot] += 1;           // (the rows of a pass are distinct slots)
         if (nB > 0) {
-            st[ST_STEPS] += 1;
-            st[ST_SUM_M] += nB;
-            if (nB > st[ST_MAX_M]) st[ST_MAX_M] = nB;
-            st[ST_HIST + (nB < 64 ? nB : 64)] += 1;
+            count(ST_STEPS, 1);
+            count(ST_SUM_M, nB);
+            count(ST_HIST + (nB < 64 ? nB : 64), 1);
         }
-        for (int q = 0; q < s.max_seqs; ++q) {
-            s.q_last_tok[q] = -1;
-            s.q_last_src[q] = -1;
-        }
+        t.last_tok[lane] = -1;
+        t.last_src[lane] = -1;
+        lds_sync();
         // ---- gate statistics: Alg. 1 evaluates the gate of every branch that
         //      reaches d2 this step, before the root's verification prunes any
         if (mode == MODE_LOOPSPEC && s.d2 > 0) {
-            for (int i = 0; i < nC; ++i) {
-                if (s.rowsC[i].depth != s.d2) continue;
-                st[ST_GATE_EVAL] += 1;
-                st[ST_GATE_OPEN] += s.ro_aux[i] ? 1 : 0;
-            }
+            const bool at = lane < nC && t.r_depth[lane] == s.d2;
+            count(ST_GATE_EVAL, __popcll(__ballot(at)));
+            count(ST_GATE_OPEN, __popcll(__ballot(at && t.ro_aux[lane] != 0)));
         }
         // ---- roots at depth R: commit, re-root, prune -----------------------
         for (int i = 0; i < nC; ++i) {
-            const Row row = s.rowsC[i];
-            if (row.depth != s.R) continue;
-            const int q = row.seq, b = row.slot, np = row.pos + 1;
-            int tok = s.ro_tok[i], src = s.ro_aux[i];
+            if (t.r_depth[i] != s.R) continue;
+            const int q = t.r_seq[i], b = t.r_slot[i], np = t.r_pos[i] + 1;
+            int tok = t.ro_tok[i], src = t.ro_aux[i];
             if (mode == MODE_FORCED) {
                 tok = s.forced[(size_t)q * ctx + np];
                 src = 0;
             } else if (mode == MODE_VANILLA) {
                 src = 0;
             }
-            s.Y[(size_t)q * ctx + np] = tok;
-            s.q_ncommit[q] += 1;
-            s.q_last_tok[q] = tok;
-            s.q_last_src[q] = src;
-            st[ST_COMMITTED] += 1;
-            if (mode == MODE_LOOPSPEC) st[src == 1 ? ST_ACC1 : src == 2 ? ST_ACC2 : ST_RESTART] += 1;
-            // greedy: TV between one-hot readouts is the argmax mismatch (the
-            // argmax at d2 is kept in s_x2 whether or not its branch was
-            // spawned; the sampled readout adds its TV sums itself)
-            if (mode == MODE_LOOPSPEC && s.greedy && s.s_x1[b] >= 0) {
-                const int x1 = s.s_x1[b], a2 = s.s_x2[b] >= 0 ? s.s_x2[b] : x1;
-                st[ST_TVN] += 1;
-                st[ST_TV1] += x1 != tok ? (1LL << 32) : 0;
-                if (s.d2 > 0) st[ST_TV2] += a2 != tok ? (1LL << 32) : 0;
+            if (lane == 0) {
+                s.Y[(size_t)q * ctx + np] = tok;
+                s.jc[3 * njc] = q;
+                s.jc[3 * njc + 1] = b;
+                s.jc[3 * njc + 2] = np - 1;
             }
-            int c = src == 1 ? s.s_c1[b] : src == 2 ? s.s_c2[b] : -1;
-            s.jc[3 * njc] = q;
-            s.jc[3 * njc + 1] = b;
-            s.jc[3 * njc + 2] = row.pos;
             ++njc;
-            for (int x = 0; x < S; ++x)
-                if (s.s_active[x] && s.s_seq[x] == q && !in_subtree(s, x, c)) s.s_active[x] = 0;
-            s.q_tdone[q] = np;
+            const int nc = t.ncommit[q] + 1;
+            t.ncommit[q] = nc;
+            t.last_tok[q] = tok;
+            t.last_src[q] = src;
+            count(ST_COMMITTED, 1);
+            if (mode == MODE_LOOPSPEC) count(src == 1 ? ST_ACC1 : src == 2 ? ST_ACC2 : ST_RESTART, 1);
+            // greedy: TV between one-hot readouts is the argmax mismatch (the
+            // argmax at d2 is kept in x2 whether or not its branch was
+            // spawned; the sampled readout adds its TV sums itself)
+            if (mode == MODE_LOOPSPEC && s.greedy && t.x1[b] >= 0) {
+                const int x1 = t.x1[b], a2 = t.x2[b] >= 0 ? t.x2[b] : x1;
+                count(ST_TVN, 1);
+                if (x1 != tok) count(ST_TV1, 1LL << 32);
+                if (s.d2 > 0 && a2 != tok) count(ST_TV2, 1LL << 32);
+            }
+            int k = src == 1 ? t.c1[b] : src == 2 ? t.c2[b] : -1;
+            const bool drop = has_slot && t.active[lane] && t.seq[lane] == q && !in_subtree(t, S, lane, k);
+            lds_sync();
+            if (drop) t.active[lane] = 0;
+            t.tdone[q] = np;
+            lds_sync();
             if (np >= ctx - 1) {                       // no room for another position
-                atomicOr(s.err, ERR_CTX);
-                s.q_state[q] = SEQ_PAUSED;
-                for (int x = 0; x < S; ++x)
-                    if (s.s_seq[x] == q) s.s_active[x] = 0;
-                s.q_root[q] = -1;
+                error(ERR_CTX);
+                t.state[q] = SEQ_PAUSED;
+                t.root[q] = -1;
+                if (has_slot && t.seq[lane] == q) t.active[lane] = 0;
+                lds_sync();
                 continue;
             }
-            if (c < 0) {
-                c = alloc_slot(s);
-                if (c < 0) {                           // cannot happen: the old root was just freed
-                    atomicOr(s.err, ERR_SLOTS);
-                    s.q_state[q] = SEQ_PAUSED;
-                    s.q_root[q] = -1;
+            if (k < 0) {
+                k = alloc_slot(t, S, lane);
+                if (k < 0) {                           // cannot happen: the old root was just freed
+                    error(ERR_SLOTS);
+                    t.state[q] = SEQ_PAUSED;
+                    t.root[q] = -1;
+                    lds_sync();
                     continue;
                 }
-                init_slot(s, c, q, np, tok, -1);
-                s.js[2 * njs] = c;
-                s.js[2 * njs + 1] = tok;
-                ++njs;
+                init_slot(t, k, q, np, tok, -1);
+                spawn(k, tok);
             }
-            s.s_parent[c] = -1;
-            s.q_root[q] = c;
-            if (s.q_ncommit[q] >= s.q_target[q]) s.q_state[q] = SEQ_PAUSED;
+            t.parent[k] = -1;
+            t.root[q] = k;
+            if (nc >= t.target[q]) t.state[q] = SEQ_PAUSED;
+            lds_sync();
         }
         // ---- proposals at d1 / d2 -----------------------------------------------
         if (mode == MODE_LOOPSPEC) {
             for (int i = 0; i < nC; ++i) {
-                const Row row = s.rowsC[i];
-                const int b = row.slot, q = row.seq;
+                const int b = t.r_slot[i], q = t.r_seq[i], pos = t.r_pos[i], dep = t.r_depth[i];
                 // the branch must still hold this slot: a slot pruned above may
                 // already carry a new root (depth 0) of the same step.  A
                 // sequence that reached its commit target in this step still
                 // records its drafts (it resumes from this tree on the next
                 // call); one whose tree was dropped has no active slot left.
-                if (!s.s_active[b] || s.s_seq[b] != q || s.s_pos[b] != row.pos || s.s_depth[b] != row.depth ||
-                    s.q_root[q] < 0)
-                    continue;
-                if (row.depth == s.d1) {
-                    const int x1 = s.ro_tok[i];
-                    s.s_x1[b] = x1;
-                    s.s_c2[b] = -1;
-                    s.s_gate[b] = 0;
-                    const int c = row.pos + 1 < ctx - 1 ? alloc_slot(s) : -1;
-                    s.s_c1[b] = c;
-                    if (c < 0) {
-                        st[ST_REFUSED] += 1;
+                if (!t.active[b] || t.seq[b] != q || t.pos[b] != pos || t.depth[b] != dep || t.root[q] < 0) continue;
+                const int x = t.ro_tok[i];
+                if (dep == s.d1) {
+                    t.x1[b] = x;
+                    t.c2[b] = -1;
+                    t.gate[b] = 0;
+                    const int k = pos + 1 < ctx - 1 ? alloc_slot(t, S, lane) : -1;
+                    t.c1[b] = k;
+                    lds_sync();
+                    if (k < 0) {
+                        count(ST_REFUSED, 1);
                         continue;
                     }
-                    init_slot(s, c, q, row.pos + 1, x1, b);
-                    s.js[2 * njs] = c;
-                    s.js[2 * njs + 1] = x1;
-                    ++njs;
-                } else if (s.d2 > 0 && row.depth == s.d2) {
-                    if (s.greedy) s.s_x2[b] = s.ro_tok[i];   // verification reads it only with the gate open
-                    if (!s.ro_aux[i]) continue;
-                    const int x2 = s.ro_tok[i];
-                    const int c = row.pos + 1 < ctx - 1 ? alloc_slot(s) : -1;
-                    if (c < 0) {                       // no room: the gate stays closed
-                        st[ST_REFUSED] += 1;
+                    init_slot(t, k, q, pos + 1, x, b);
+                    spawn(k, x);
+                } else if (s.d2 > 0 && dep == s.d2) {
+                    if (s.greedy) t.x2[b] = x;         // verification reads it only with the gate open
+                    lds_sync();
+                    if (!t.ro_aux[i]) continue;
+                    const int k = pos + 1 < ctx - 1 ? alloc_slot(t, S, lane) : -1;
+                    if (k < 0) {                       // no room: the gate stays closed
+                        count(ST_REFUSED, 1);
                         continue;
                     }
-                    s.s_gate[b] = 1;
-                    s.s_x2[b] = x2;
-                    s.s_c2[b] = c;
-                    init_slot(s, c, q, row.pos + 1, x2, b);
-                    s.js[2 * njs] = c;
-                    s.js[2 * njs + 1] = x2;
-                    ++njs;
+                    t.gate[b] = 1;
+                    t.x2[b] = x;
+                    t.c2[b] = k;
+                    init_slot(t, k, q, pos + 1, x, b);
+                    spawn(k, x);
                 }
             }
         }
@@ -214,84 +287,79 @@ __global__ void k_sched(Sched s, int op, int op_seq, int op_pos, const int32_t* 
         // has computed (they do not depend on d1, d2); one at or past it
         // restarts at depth 0 from its embedding, so that it drafts at the new
         // d1 (its hidden states and slot keys / values are recomputed)
-        const int q = op_seq, c = s.q_root[q];
-        if (c >= 0) {
-            for (int x = 0; x < S; ++x)
-                if (x != c && s.s_active[x] && s.s_seq[x] == q) s.s_active[x] = 0;
-            const int depth = s.s_depth[c];
-            init_slot(s, c, q, s.s_pos[c], s.s_tok[c], -1);
-            if (depth < s.d1) {
-                s.s_depth[c] = depth;
-            } else {
-                s.js[0] = c;
-                s.js[1] = s.s_tok[c];
-                njs = 1;
-            }
+        const int q = op_seq, r = t.root[q];
+        if (r >= 0) {
+            if (has_slot && lane != r && t.active[lane] && t.seq[lane] == q) t.active[lane] = 0;
+            const int depth = t.depth[r], pos = t.pos[r], tok = t.tok[r];
+            lds_sync();
+            init_slot(t, r, q, pos, tok, -1);
+            if (depth < s.d1)
+                t.depth[r] = depth;
+            else
+                spawn(r, tok);
         }
     } else if (op == OP_INIT) {
-        const int q = op_seq, n = op_pos, tok = op_tok[0];
-        for (int x = 0; x < S; ++x)
-            if (s.s_seq[x] == q) s.s_active[x] = 0;
-        const int c = alloc_slot(s);
-        if (c < 0) {
-            atomicOr(s.err, ERR_SLOTS);
+        const int q = op_seq, n = op_pos;
+        if (has_slot && t.seq[lane] == q) t.active[lane] = 0;
+        lds_sync();
+        const int k = alloc_slot(t, S, lane);
+        if (k < 0) {
+            error(ERR_SLOTS);
         } else {
-            init_slot(s, c, q, n, tok, -1);
-            s.q_root[q] = c;
-            s.q_tdone[q] = n;
-            s.q_ncommit[q] = 1;
-            s.q_state[q] = SEQ_PAUSED;
-            s.Y[(size_t)q * ctx + n] = tok;
-            s.js[0] = c;
-            s.js[1] = tok;
-            njs = 1;
+            init_slot(t, k, q, n, tok0, -1);
+            t.root[q] = k;
+            t.tdone[q] = n;
+            t.ncommit[q] = 1;
+            t.state[q] = SEQ_PAUSED;
+            if (lane == 0) s.Y[(size_t)q * ctx + n] = tok0;
+            spawn(k, tok0);
         }
     }
+    lds_sync();
 
-    // ---- next pass: rows of every live branch, grouped by sequence -------------
-    int nB = 0, nC = 0, nP = 0;
-    for (int q = 0; q < s.max_seqs; ++q) {
-        if (s.q_state[q] != SEQ_LIVE) continue;
-        const int tdone = s.q_tdone[q];
-        for (int x = 0; x < S; ++x) {
-            if (!s.s_active[x] || s.s_seq[x] != q) continue;
-            Row r;
-            r.xrow = x;
-            r.slot = x;
-            r.seq = q;
-            r.pos = s.s_pos[x];
-            r.depth = s.s_depth[x] + 1;
-            r.tdone = tdone;
-            r.src = x;                                   // copy source for readout rows
-            r.pad = 0;
-            fill_chain(s, x, tdone, r);
-            s.rowsB[nB++] = r;
-            if (is_readout(s, mode, r.depth)) {
-                if (s.coda_xrow0 >= 0) r.xrow = s.coda_xrow0 + nC;
-                s.rowsC[nC++] = r;
+    // ---- next pass: rows of every live branch, grouped by sequence, slots ascending
+    const int q = has_slot ? t.seq[lane] : -1;
+    const bool live = has_slot && t.active[lane] && q >= 0 && q < Q && t.state[q] == SEQ_LIVE;
+    const int dn = has_slot ? t.depth[lane] + 1 : 0;
+    const bool ro = live && is_readout(s, mode, dn);
+    const unsigned long long below = (1ull << lane) - 1;
+    int nB = 0, nC = 0, ib = 0, ic = 0;
+    for (int k = 0; k < Q; ++k) {
+        const unsigned long long mb = __ballot(live && q == k), mc = __ballot(ro && q == k);
+        if (q == k) {
+            ib = nB + __popcll(mb & below);
+            ic = nC + __popcll(mc & below);
+        }
+        nB += __popcll(mb);
+        nC += __popcll(mc);
+    }
+    if (live) put_row(t, lane, dn, lane, s.rowsB + ib, s.err);
+    if (ro) put_row(t, lane, dn, s.coda_xrow0 >= 0 ? s.coda_xrow0 + ic : lane, s.rowsC + ic, s.err);
+    if (lane < njs) put_row(t, t.js[2 * lane], 0, t.js[2 * lane], s.rowsP + lane, s.err);
+    // ---- the tables back
+    for (int i = lane; i < 2 * njs; i += 64) s.js[i] = t.js[i];
+#pragma unroll
+    for (int i = 0; i < 11; ++i)
+        if (has_slot) slot_g[i][lane] = slot_l[i][lane];
+    // (targets are the host's)
+#pragma unroll
+    for (int i = 0; i < 7; ++i)
+        if (has_seq && i != 3) seq_g[i][lane] = seq_l[i][lane];
+    if (op == OP_STEP)
+        for (int i = lane; i < ST_N; i += 64) {
+            if (i == ST_MAX_M) {
+                if (nB0 > s.stats[i]) s.stats[i] = nB0;
+            } else if (st[i]) {
+                s.stats[i] += st[i];
             }
         }
+    if (lane == 0) {
+        *s.nB = nB;
+        *s.nC = nC;
+        *s.nP = njs;
+        *s.njc = njc;
+        *s.njs = njs;
     }
-    for (int j = 0; j < njs; ++j) {
-        const int x = s.js[2 * j];
-        const int q = s.s_seq[x];
-        Row r;
-        r.xrow = x;
-        r.slot = x;
-        r.seq = q;
-        r.pos = s.s_pos[x];
-        r.depth = 0;
-        r.tdone = s.q_tdone[q];
-        r.src = x;
-        r.pad = 0;
-        fill_chain(s, x, r.tdone, r);
-        s.rowsP[nP++] = r;
-    }
-    *s.nB = nB;
-    *s.nC = nC;
-    *s.nP = nP;
-    *s.njc = njc;
-    *s.njs = njs;
 }
 
 hipError_t launch_sched(const Sched& s, int op, int op_seq, int op_pos, const int32_t* op_tok, hipStream_t st) {
