@@ -446,7 +446,7 @@ int loopspec_cascade(const loopspec_cascade_cfg* cfg, int32_t rows, const float*
  * device memory (code under HIP graph capture, serving loops, harnesses that
  * forbid hipMalloc): the same decisions, bit for bit, with the barrier state
  * kept in a static device array of the library (2.2 MiB: 64 rows in flight,
- * longer row lists run in launches of 64 rows) that each GPU holds until the
+ * the rows of longer lists follow each other) that each GPU holds until the
  * process ends.  Allocates nothing.  Every call on one GPU shares that GPU's
  * array, so calls that overlap on one GPU (other host threads, other streams)
  * race and must not be issued; consecutive calls are fine (each clears the

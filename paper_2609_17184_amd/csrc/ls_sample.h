@@ -47,8 +47,8 @@ constexpr int kRowPart = 8;
 constexpr int kRowHist = kRowPart + 2 * kSShardsMax * kPartSlots;
 constexpr int kRowWords = kRowHist + kHistWords;
 
-// Rows one launch of the standalone cascade handles when a row takes several
-// shards (so that every shard of every row in flight is resident at once).
+// Rows the standalone cascade has in flight when a row takes several shards
+// (every shard of every row in flight is resident at once).
 constexpr int kCascadeRowsPerLaunch = 64;
 
 // decode steps: the sampled readout of every C row (Alg. 1 proposals and

@@ -543,7 +543,11 @@ struct RowOut {
     unsigned long long tv1, tv2;
 };
 
-template <int E>
+// FUSED: the row's roles follow each other in one launch.  q1 and q2 then were
+// written by this launch, each id by the thread that owns it, and a value at
+// one id travels from its owner through the barrier's slots; else earlier
+// launches wrote them and every thread may read any id.
+template <int E, bool FUSED = false>
 __device__ __forceinline__ RowOut sample_row(SCtx& c, const SampleCfg& cfg, const RowJob& j) {
     RowOut o{-1, 0, 0, 0, 0, 0ull, 0ull};
     if (j.role == ROLE_NONE) return o;
@@ -587,6 +591,7 @@ __device__ __forceinline__ RowOut sample_row(SCtx& c, const SampleCfg& cfg, cons
         publish(c, 2, px1);
         publish(c, 3, rx1);
         publish(c, 4, px1f);
+        if (FUSED) publish(c, 5, wg_owner_u64(own1, own1 ? __float_as_uint(j.q1[x1]) : 0u, c));
         row_sync(c);
         const unsigned long long gS = gather_sum(c, 0), gP = gather_sum(c, 1);
         const float gpx1 = __uint_as_float((unsigned)gather_sum(c, 2));
@@ -594,7 +599,7 @@ __device__ __forceinline__ RowOut sample_row(SCtx& c, const SampleCfg& cfg, cons
         bool open;
         float q2[E];
         if (cfg.variant == LOOPSPEC_SP_GATED) {
-            open = gpx1 < j.q1[x1];                  // q2~(x1) < q1(x1)
+            open = gpx1 < (FUSED ? __uint_as_float((unsigned)gather_sum(c, 5)) : j.q1[x1]);   // q2~(x1) < q1(x1)
             if (open) {
                 const bool zm = gS == 0;
                 o.zero_mass = zm;
@@ -642,20 +647,24 @@ __device__ __forceinline__ RowOut sample_row(SCtx& c, const SampleCfg& cfg, cons
     if (gate) {
         publish(c, 2, wg_owner_u64(own2, __float_as_uint(pick(c, r, x2)), c));
         publish(c, 3, wg_owner_u64(own2, __float_as_uint(pick(c, p, x2)), c));
+        if (FUSED) publish(c, 4, wg_owner_u64(own2, own2 ? __float_as_uint(j.q2[x2]) : 0u, c));
     } else {
         // without a second proposal a rejection resamples from rho1: race
         // [p - q1]_+ now (and p, in case it has no positive mass)
         publish(c, 4, race_key(c, r, cfg.seed, j.seq, j.pos, EV_RESAMPLE));
         publish(c, 5, race_key(c, p, cfg.seed, j.seq, j.pos, EV_RESAMPLE));
     }
+    if (FUSED) publish(c, 7, wg_owner_u64(own1, own1 ? __float_as_uint(j.q1[x1]) : 0u, c));
     row_sync(c);
+    const float q1x1 = FUSED ? __uint_as_float((unsigned)gather_sum(c, 7)) : j.q1[x1];
+    const float q2x2 = !gate ? 0.f : FUSED ? __uint_as_float((unsigned)gather_sum(c, 4)) : j.q2[x2];
     const unsigned long long gS1 = gather_sum(c, 0);
     const float gpx1 = __uint_as_float((unsigned)gather_sum(c, 1));
     o.has_tv = 1;
     o.tv1 = gS1;                                 // sum [p - q1]_+ = TV(p, q1)
     o.tv2 = j.q2t ? gather_sum(c, 6) : 0ull;
     const float u1 = accept_u(cfg.seed, j.seq, j.pos, EV_ACC1);
-    if (u1 < fminf(1.0f, gpx1 / j.q1[x1])) {
+    if (u1 < fminf(1.0f, gpx1 / q1x1)) {
         o.tok = x1;
         o.aux = 1;
         return o;
@@ -670,7 +679,7 @@ __device__ __forceinline__ RowOut sample_row(SCtx& c, const SampleCfg& cfg, cons
     const float rho_x2 = zm1 ? __uint_as_float((unsigned)gather_sum(c, 3))
                              : __uint_as_float((unsigned)gather_sum(c, 2)) * invS1;
     const float u2 = accept_u(cfg.seed, j.seq, j.pos, EV_ACC2);
-    if (u2 < fminf(1.0f, rho_x2 / j.q2[x2])) {
+    if (u2 < fminf(1.0f, rho_x2 / q2x2)) {
         o.tok = x2;
         o.aux = 2;
         return o;
@@ -815,59 +824,105 @@ hipError_t launch_zero_words(unsigned long long* p, size_t n, hipStream_t st) {
 }
 
 // ---------------------------------------------------------------------------
-// standalone cascade over independent keyed positions (one launch per role)
+// standalone cascade over independent keyed positions: one launch
+//
+// NS workgroups hold a place; place l takes rows l, l + places, ... and runs
+// the row's three roles one after the other (x1, the gate and x2 stay in
+// registers: every shard takes the same decisions).  A row is a chain of about
+// twenty row barriers, each a round trip or two through memory, so the launch
+// is bound by latency; with a launch per role and 64 rows, 12 launches for 256
+// rows, every chain also waited for the slowest row of its launch three times
+// and the chip drained in between, and no row's loads ran under another's
+// chain.  The whole call, 4 rows of V = 4096: 113 -> 85 us; 256 rows of 65536
+// with top-p 0.95: 1023 -> 974 us, where the arithmetic of the races and the
+// histogram atomics of four workgroups per CU take over from the barriers.
 // ---------------------------------------------------------------------------
 struct CascadeArgs {
-    int rows, row0;
-    const float* z;              // logits of this role's depth, row i at z + i * zstride
+    int rows, places, has_second;
+    const float *z1, *z2, *zR;   // readout logits, row i at + i * zstride
     long long zstride;
     float *q1, *q2;              // [rows][V]
     const int32_t* keys;         // [rows][2]: sequence, position
     int32_t* out;                // [rows][6]: token, source, x1, gate, x2, zero-mass events
-    unsigned long long* scratch; // kRowWords per row of the launch (row - row0), NS > 1
+    unsigned long long* scratch; // kRowWords per place, NS > 1
     int32_t* err;
     int vec;                     // 16-byte accesses allowed (rows and pointers 16-byte aligned)
 };
 
+// The histograms of a row's last top-p cut back to zero, this shard's share.
+// Every shard has read them: a row barrier lies behind the cut.  The next cut
+// adds to them only behind another one, which waits for these stores.
+__device__ __forceinline__ void clear_hist(const SCtx& c) {
+    if (c.NS == 1) return;
+    for (int i = c.s * kSThreads + threadIdx.x; i < kHistWords; i += c.NS * kSThreads)
+        __hip_atomic_store(c.rw + kRowHist + i, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
 template <int E>
-__global__ void __launch_bounds__(kSThreads) k_cascade(SampleCfg cfg, CascadeArgs a, int role, int V) {
+__global__ void __launch_bounds__(kSThreads) __attribute__((amdgpu_waves_per_eu(4))) k_cascade(SampleCfg cfg, CascadeArgs a, int V) {
     const SGeo g = sample_geo(V);
-    const int li = blockIdx.x / g.NS, shard = blockIdx.x - li * g.NS;
-    const int i = a.row0 + li;
-    if (i >= a.rows) return;
+    const int l = blockIdx.x / g.NS, shard = blockIdx.x - l * g.NS;
     __shared__ SLds lds;
-    SCtx c = make_ctx(g, shard, g.NS > 1 ? a.scratch + (size_t)li * kRowWords : nullptr, a.err, &lds);
+    SCtx c = make_ctx(g, shard, g.NS > 1 ? a.scratch + (size_t)l * kRowWords : nullptr, a.err, &lds);
     c.v4 = c.v4 && a.vec;
-    int32_t* o = a.out + (size_t)i * 6;
-    RowJob j{};
-    j.role = role;
-    j.z = a.z + (size_t)i * a.zstride;
-    j.q1 = a.q1 + (size_t)i * V;
-    j.q2 = a.q2 + (size_t)i * V;
-    j.seq = a.keys[2 * i];
-    j.pos = a.keys[2 * i + 1];
-    j.x1 = role == ROLE_DRAFT1 ? -1 : o[2];
-    j.gate = o[3];
-    j.x2 = o[4];
-    const RowOut r = sample_row<E>(c, cfg, j);
-    if (shard == 0 && threadIdx.x == 0) {
-        if (role == ROLE_DRAFT1) {
-            o[2] = r.tok;
-            o[3] = 0;
-            o[4] = -1;
-            o[5] = r.zero_mass;
-        } else if (role == ROLE_DRAFT2) {
-            o[3] = r.aux;
-            o[4] = r.aux ? r.tok : -1;
-            o[5] += r.zero_mass;
-        } else {
-            o[0] = r.tok;
-            o[1] = r.aux;
-            o[5] += r.zero_mass;
+    for (int i = l; i < a.rows; i += a.places) {
+        RowJob j{};
+        j.q1 = a.q1 + (size_t)i * V;
+        j.q2 = a.q2 + (size_t)i * V;
+        j.seq = a.keys[2 * i];
+        j.pos = a.keys[2 * i + 1];
+        j.x1 = j.x2 = -1;
+        int zero = 0, bad = 0, tok = -1, src = 0;
+        // (one loop, one copy of the roles' code: three took 210 registers at E = 16, two workgroups a CU)
+#pragma nounroll
+        for (int k = 0; k < 3; ++k) {
+            if (k == 1 && !a.has_second) continue;
+            // (opaque: what depends on the thread's ids alone, the first Philox
+            // products among it, is not held in registers across the roles)
+            // (163 registers at E = 16 before the bound of four workgroups a CU, 251 without it)
+            asm volatile("" : "+v"(c.lo), "+v"(c.hi));
+            j.role = k == 0 ? ROLE_DRAFT1 : k == 1 ? ROLE_DRAFT2 : ROLE_VERIFY;
+            j.z = (k == 0 ? a.z1 : k == 1 ? a.z2 : a.zR) + (size_t)i * a.zstride;
+            const RowOut r = sample_row<E, true>(c, cfg, j);
+            if (r.bad) row_sync(c);              // (the one way out without a barrier behind the cut)
+            if (cfg.top_p < 1.0f) clear_hist(c);
+            zero += r.zero_mass;
+            bad |= r.bad;
+            if (k == 0) {
+                j.x1 = r.tok;
+            } else if (k == 1) {
+                j.gate = r.aux;
+                j.x2 = r.aux ? r.tok : -1;
+            } else {
+                tok = r.tok;
+                src = r.aux;
+            }
         }
-        if (r.bad) atomicOr(a.err, ERR_TREE);
+        if (shard == 0 && threadIdx.x == 0) {
+            int32_t* o = a.out + (size_t)i * 6;
+            o[0] = tok;
+            o[1] = src;
+            o[2] = j.x1;
+            o[3] = j.gate;
+            o[4] = j.x2;
+            o[5] = zero;
+            if (bad) atomicOr(a.err, ERR_TREE);
+        }
     }
     row_exit(c);
+}
+
+template <int E>
+static int cascade_places(const SGeo& g, const void** f) {
+    *f = (const void*)k_cascade<E>;
+    int dev = 0, cus = 0, per = 0;
+    if (hipGetDevice(&dev) != hipSuccess ||
+        hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
+        hipOccupancyMaxActiveBlocksPerMultiprocessor(&per, *f, kSThreads, 0) != hipSuccess) {
+        (void)hipGetLastError();
+        return 0;
+    }
+    return cus * per / g.NS;
 }
 
 }  // namespace ls
@@ -918,23 +973,37 @@ int cascade_check(const loopspec_cascade_cfg* cfg, int32_t rows, const float* z1
     return LOOPSPEC_OK;
 }
 
-// The three roles over every row, in launches of kCascadeRowsPerLaunch rows
-// when a row takes several shards.  `rw` holds kRowWords per row of a launch
-// and one more word for the error flag.
+// Every row in one launch, on up to kCascadeRowsPerLaunch places when a row
+// takes several shards (all resident at once: they wait for each other).  `rw`
+// holds kRowWords per place and one more word for the error flag.
 int cascade_run(const loopspec_cascade_cfg* cfg, int32_t rows, const float* z1, const float* z2, const float* zR,
                 int64_t zstride, const int32_t* keys, int32_t* out, float* q1, float* q2, unsigned long long* rw,
                 hipStream_t st) {
     if (!rows) return LOOPSPEC_OK;
     const SGeo g = sample_geo(cfg->vocab);
-    const int per = g.NS > 1 ? kCascadeRowsPerLaunch : rows;
-    if (g.NS > 1 && sample_rows_resident(cfg->vocab) < kCascadeRowsPerLaunch) return LOOPSPEC_EHIP;
-    const size_t words = g.NS > 1 ? (size_t)std::min(rows, per) * kRowWords : 0;
+    const void* f = nullptr;
+    int places = 0;
+    switch (g.E) {
+        case 4: places = cascade_places<4>(g, &f); break;
+        case 8: places = cascade_places<8>(g, &f); break;
+        case 12: places = cascade_places<12>(g, &f); break;
+        case 16: places = cascade_places<16>(g, &f); break;
+        default: return LOOPSPEC_EINVAL;
+    }
+    places = g.NS > 1 ? std::min(std::min(rows, kCascadeRowsPerLaunch), places) : rows;
+    if (places < 1) return LOOPSPEC_EHIP;
+    const size_t words = g.NS > 1 ? (size_t)std::min(rows, kCascadeRowsPerLaunch) * kRowWords : 0;
     int32_t* err = (int32_t*)(rw + words);
     // barrier state and the error word start at zero (a fill kernel, not a memset)
     if (launch_zero_words(rw, words + 1, st) != hipSuccess) return LOOPSPEC_EHIP;
     SampleCfg sc{cfg->temperature, cfg->top_p, cfg->second_proposal, (unsigned long long)cfg->seed};
     CascadeArgs a{};
     a.rows = rows;
+    a.places = places;
+    a.has_second = cfg->has_second != 0;
+    a.z1 = z1;
+    a.z2 = z2;
+    a.zR = zR;
     a.zstride = zstride;
     a.q1 = q1;
     a.q2 = q2;
@@ -944,25 +1013,9 @@ int cascade_run(const loopspec_cascade_cfg* cfg, int32_t rows, const float* z1, 
     a.err = err;
     auto al = [](const void* q) { return ((uintptr_t)q & 15) == 0; };
     a.vec = (zstride & 3) == 0 && al(z1) && al(zR) && (!z2 || al(z2)) && al(q1) && al(q2);
-    const int roles[3] = {ROLE_DRAFT1, ROLE_DRAFT2, ROLE_VERIFY};
-    const float* zs[3] = {z1, z2, zR};
-    for (int r0 = 0; r0 < rows; r0 += per) {
-        const int n = std::min(per, rows - r0);
-        a.row0 = r0;
-        for (int k = 0; k < 3; ++k) {
-            if (roles[k] == ROLE_DRAFT2 && !cfg->has_second) continue;
-            a.z = zs[k];
-            const dim3 grid(n * g.NS), blk(kSThreads);
-            switch (g.E) {
-                case 4: hipLaunchKernelGGL(k_cascade<4>, grid, blk, 0, st, sc, a, roles[k], cfg->vocab); break;
-                case 8: hipLaunchKernelGGL(k_cascade<8>, grid, blk, 0, st, sc, a, roles[k], cfg->vocab); break;
-                case 12: hipLaunchKernelGGL(k_cascade<12>, grid, blk, 0, st, sc, a, roles[k], cfg->vocab); break;
-                case 16: hipLaunchKernelGGL(k_cascade<16>, grid, blk, 0, st, sc, a, roles[k], cfg->vocab); break;
-                default: return LOOPSPEC_EINVAL;
-            }
-            if (hipGetLastError() != hipSuccess) return LOOPSPEC_EHIP;
-        }
-    }
+    int V = cfg->vocab;
+    void* args[] = {(void*)&sc, (void*)&a, (void*)&V};
+    if (hipLaunchKernel(f, dim3(places * g.NS), dim3(kSThreads), args, 0, st) != hipSuccess) return LOOPSPEC_EHIP;
     int32_t e = 0;
     if (hipMemcpyAsync(&e, err, 4, hipMemcpyDeviceToHost, st) != hipSuccess || hipStreamSynchronize(st) != hipSuccess)
         return LOOPSPEC_EHIP;
