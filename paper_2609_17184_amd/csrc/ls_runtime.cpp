@@ -12,6 +12,7 @@
 #include <cmath>
 #include <cstdio>
 #include <cstring>
+#include <numeric>
 #include <string>
 #include <vector>
 
@@ -160,6 +161,8 @@ struct loopspec_handle {
     hipGraphExec_t exec = nullptr;
     hipGraph_t graph4 = nullptr;      // kStepsPerGraph steps back to back
     hipGraphExec_t exec4 = nullptr;
+    hipGraph_t graphq[2] = {nullptr, nullptr};       // one and kStepsPerGraph quiet steps (prelude / coda models)
+    hipGraphExec_t execq[2] = {nullptr, nullptr};
     int tree_mode = MODE_LOOPSPEC;
     float* skpart = nullptr;           // stream-K GEMM partials handed between waves (sentinel between launches)
     size_t skpart_n = 0;
@@ -487,10 +490,16 @@ hipError_t enqueue_finalize(loopspec_t h, const Sched& s, int fin_op, int rows_c
     return launch_finalize_sample(s, fin_op, h->logits, rows_cap, h->st);
 }
 
-// The whole decode step (captured once into a graph).
-hipError_t enqueue_step(loopspec_t h) {
+// The whole decode step (captured once into a graph).  quiet: a step known to
+// have no readout row: it spawns and commits nothing, so every launch but the
+// core stack's and the scheduler's would find an empty list.
+hipError_t enqueue_step(loopspec_t h, bool quiet = false) {
     Sched& s = h->sch;
     hipError_t e;
+    if (quiet) {
+        if ((e = enqueue_stack(h, STACK_CORE, s.rowsB, s.nB, h->S)) != hipSuccess) return e;
+        return launch_sched(s, OP_STEP, 0, 0, nullptr, h->st);
+    }
     if ((e = enqueue_stack(h, STACK_CORE, s.rowsB, s.nB, h->S)) != hipSuccess) return e;
     if (h->g.Lc) {
         if ((e = launch_copy_rows(h->g, s.rowsC, s.nC, h->S, h->X, h->st)) != hipSuccess) return e;
@@ -512,10 +521,10 @@ hipError_t enqueue_step(loopspec_t h) {
 // between them on the GPU, so long decodes replay the multi-step graph.
 constexpr int kStepsPerGraph = 4;
 
-static int capture_steps(loopspec_t h, int steps, hipGraph_t* graph, hipGraphExec_t* exec) {
+static int capture_steps(loopspec_t h, int steps, hipGraph_t* graph, hipGraphExec_t* exec, bool quiet = false) {
     HIPCHK(h, hipStreamBeginCapture(h->st, hipStreamCaptureModeThreadLocal));
     hipError_t e = hipSuccess;
-    for (int i = 0; i < steps && e == hipSuccess; ++i) e = enqueue_step(h);
+    for (int i = 0; i < steps && e == hipSuccess; ++i) e = enqueue_step(h, quiet);
     hipGraph_t g = nullptr;
     hipError_t e2 = hipStreamEndCapture(h->st, &g);
     if (e != hipSuccess) return fail(h, LOOPSPEC_EHIP, std::string("step capture: ") + hipGetErrorString(e));
@@ -534,13 +543,22 @@ void drop_graphs(loopspec_t h) {
     if (h->graph4) (void)hipGraphDestroy(h->graph4);
     h->exec = h->exec4 = nullptr;
     h->graph = h->graph4 = nullptr;
+    for (int i = 0; i < 2; ++i) {
+        if (h->execq[i]) (void)hipGraphExecDestroy(h->execq[i]);
+        if (h->graphq[i]) (void)hipGraphDestroy(h->graphq[i]);
+        h->execq[i] = nullptr;
+        h->graphq[i] = nullptr;
+    }
 }
 
 int ensure_graph(loopspec_t h) {
     if (h->exec) return LOOPSPEC_OK;
     int r = capture_steps(h, 1, &h->graph, &h->exec);
     if (r) return r;
-    return capture_steps(h, kStepsPerGraph, &h->graph4, &h->exec4);
+    if ((r = capture_steps(h, kStepsPerGraph, &h->graph4, &h->exec4))) return r;
+    if (!(h->g.Lp || h->g.Lc)) return LOOPSPEC_OK;
+    if ((r = capture_steps(h, 1, &h->graphq[0], &h->execq[0], true))) return r;
+    return capture_steps(h, kStepsPerGraph, &h->graphq[1], &h->execq[1], true);
 }
 
 int check_err(loopspec_t h) {
@@ -756,6 +774,7 @@ int loopspec_create(const loopspec_dims* dims, const loopspec_config* cfg, void*
     s.njc = s.nB + 3;
     s.njs = s.nB + 4;
     s.err = s.nB + 5;
+    s.quiet = s.nB + 6;
     s.coda_xrow0 = g.Lc ? h->xrow_coda : -1;
     if ((r = dalloc(h, &s.ro_tok, S))) return r;
     if ((r = dalloc(h, &s.ro_aux, S))) return r;
@@ -1202,6 +1221,19 @@ static int run_until(loopspec_t h, int mode, int n_tokens, const std::vector<int
     HIPCHK(h, hipEventRecord(h->ev0, h->st));
     long long launched = 0;
     const long long cap = (long long)(n_tokens + 2) * h->c.R * 4 + 64;
+    // Models with prelude or coda blocks launch those blocks, the head and the
+    // commit with empty lists in every step that reads nothing out: about 27
+    // launches, 75 us of a Raven-shaped step of 850.  Between two readouts the
+    // tree does not change, so the host asks the scheduler how far the next one
+    // is (about 30 us) and replays the short step until then.  A sequence's
+    // branches start at each other's readouts, so its readouts lie on multiples
+    // of gap = gcd(d1, d2, R) steps; from 4 on three short steps or more pay
+    // for each question.  Several sequences read out at steps of their own,
+    // where asking would gain nothing: they keep the unconditional replay.
+    // (16, 24) of R = 32, 8 tokens: 109.0 -> 104.5 ms.
+    const int gap = mode == MODE_LOOPSPEC ? std::gcd(std::gcd(h->c.d1, h->c.d2), h->c.R) : h->c.R;
+    const int seqs = (int)std::count_if(h->prompt_len.begin(), h->prompt_len.end(), [](int n) { return n > 0; });
+    const bool by_event = h->execq[1] && seqs == 1 && gap >= 4;
     for (;;) {
         HIPCHK(h, hipMemcpyAsync(nc.data(), s.q_ncommit, 4 * Q, hipMemcpyDeviceToHost, h->st));
         HIPCHK(h, hipStreamSynchronize(h->st));
@@ -1214,6 +1246,20 @@ static int run_until(loopspec_t h, int mode, int n_tokens, const std::vector<int
         if (!remaining) break;
         int r = check_err(h);
         if (r) return r;
+        if (by_event) {
+            // the quiet steps up to the next readout without the launches that
+            // have nothing to do, the step that reads out, and back to the tree
+            int32_t quiet = 0;
+            HIPCHK(h, hipMemcpyAsync(&quiet, s.quiet, 4, hipMemcpyDeviceToHost, h->st));
+            HIPCHK(h, hipStreamSynchronize(h->st));
+            int i = 0;
+            for (; i + kStepsPerGraph <= quiet; i += kStepsPerGraph) HIPCHK(h, hipGraphLaunch(h->execq[1], h->st));
+            for (; i < quiet; ++i) HIPCHK(h, hipGraphLaunch(h->execq[0], h->st));
+            HIPCHK(h, hipGraphLaunch(h->exec, h->st));
+            launched += quiet + 1;
+            if (launched > cap) return fail(h, LOOPSPEC_ESTATE, "decode made no progress");
+            continue;
+        }
         int k = mode == MODE_LOOPSPEC ? std::max(1, (remaining - 1) * h->c.d1) : remaining * h->c.R;
         int i = 0;
         for (; i + kStepsPerGraph <= k && h->exec4; i += kStepsPerGraph) HIPCHK(h, hipGraphLaunch(h->exec4, h->st));

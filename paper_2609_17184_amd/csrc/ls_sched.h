@@ -52,6 +52,7 @@ struct Sched {
     // jobs produced by a step
     int32_t *jc, *njc;   // KV commits: (seq, slot, pos)
     int32_t *js, *njs;   // embeddings: (xrow, token)
+    int32_t* quiet;      // steps from the next one on that have no readout row (so no spawn and no commit either)
     long long* stats;
     int32_t* err;
     // sampling state (temperature > 0): per slot proposal distributions

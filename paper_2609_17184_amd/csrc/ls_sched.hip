@@ -333,6 +333,13 @@ __global__ void __launch_bounds__(64) k_sched(Sched s, int op, int op_seq, int o
         nB += __popcll(mb);
         nC += __popcll(mc);
     }
+    // steps until a live branch reads out: to its next readout depth, at or past the next pass's
+    int quiet = 0x7FFFFFFF;
+    if (live)
+        quiet = mode == MODE_FORCED ? 0
+                                    : (mode == MODE_VANILLA || dn > (s.d2 > 0 ? s.d2 : s.d1) ? s.R : dn <= s.d1 ? s.d1 : s.d2) - dn;
+#pragma unroll
+    for (int o = 32; o >= 1; o >>= 1) quiet = min(quiet, __shfl_xor(quiet, o));
     if (live) put_row(t, lane, dn, lane, s.rowsB + ib, s.err);
     if (ro) put_row(t, lane, dn, s.coda_xrow0 >= 0 ? s.coda_xrow0 + ic : lane, s.rowsC + ic, s.err);
     if (lane < njs) put_row(t, t.js[2 * lane], 0, t.js[2 * lane], s.rowsP + lane, s.err);
@@ -359,6 +366,7 @@ __global__ void __launch_bounds__(64) k_sched(Sched s, int op, int op_seq, int o
         *s.nP = njs;
         *s.njc = njc;
         *s.njs = njs;
+        *s.quiet = nB ? max(quiet, 0) : 0;
     }
 }
 
