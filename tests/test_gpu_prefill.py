@@ -11,6 +11,7 @@ import synth
 from gpu_common import MARGIN, TOL, log, model, oracle_lm, prompt
 from oracle import model as OM
 from paper_2609_17184_amd import Decoder
+from prompt_models import REL, SINK_NATS, readouts, rel, sink_model, sink_prompt, sink_spec
 
 pytestmark = pytest.mark.gpu
 
@@ -72,3 +73,23 @@ def test_prompt_of_many_query_blocks():
     spec = synth.ModelSpec(256, 16, 16, 256, 304, 0, 1, 0, R=2, alpha=0.3)
     w = synth.make_weights(spec, seed=0)
     check(spec, w, OM.LoopedLM(spec, w), 2100, 2200)
+
+
+def off(spec, w, pr, tok, max_ctx):
+    """Relative error of the readouts of one position behind a prompt."""
+    want = readouts(OM.LoopedLM(spec, w), pr, tok)
+    dec = Decoder(spec, w, R=spec.R, d1=1, d2=0, max_seqs=1, max_ctx=max_ctx)
+    dec.prefill(0, pr)
+    got, _ = dec.forced_readout(0, [tok])
+    dec.close()
+    e = rel(got[0], want)
+    log(f"[prefill] {len(pr)} positions of {spec.n_heads} x {spec.head_dim}: off by {e}")
+    return e.max()
+
+
+@pytest.mark.parametrize("dh", [16, 64, 96, 128])
+def test_prompt_small_weights(dh):
+    """Attention outputs made of weights 2^-27 below the row's largest: a key of no value far above the others.  A
+    score of SINK_NATS is a sum of products of two factors rounded at 2^-11 each."""
+    spec = sink_spec(dh=dh)
+    assert off(spec, sink_model(spec), sink_prompt(spec), 5, 200) < REL + 2 * SINK_NATS * 2.0 ** -11
