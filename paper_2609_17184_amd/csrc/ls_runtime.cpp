@@ -555,9 +555,14 @@ int ensure_graph(loopspec_t h) {
     if (h->exec) return LOOPSPEC_OK;
     int r = capture_steps(h, 1, &h->graph, &h->exec);
     if (r) return r;
-    if ((r = capture_steps(h, kStepsPerGraph, &h->graph4, &h->exec4))) return r;
-    if (!(h->g.Lp || h->g.Lc)) return LOOPSPEC_OK;
-    if ((r = capture_steps(h, 1, &h->graphq[0], &h->execq[0], true))) return r;
+    return capture_steps(h, kStepsPerGraph, &h->graph4, &h->exec4);
+}
+
+// (captured by the decodes that replay them)
+int ensure_quiet_graphs(loopspec_t h) {
+    if (h->execq[1]) return LOOPSPEC_OK;
+    int r = capture_steps(h, 1, &h->graphq[0], &h->execq[0], true);
+    if (r) return r;
     return capture_steps(h, kStepsPerGraph, &h->graphq[1], &h->execq[1], true);
 }
 
@@ -1218,7 +1223,6 @@ static int run_until(loopspec_t h, int mode, int n_tokens, const std::vector<int
     const int Q = h->d.max_seqs;
     Sched& s = h->sch;
     std::vector<int32_t> nc(Q);
-    HIPCHK(h, hipEventRecord(h->ev0, h->st));
     long long launched = 0;
     const long long cap = (long long)(n_tokens + 2) * h->c.R * 4 + 64;
     // Models with prelude or coda blocks launch those blocks, the head and the
@@ -1233,7 +1237,10 @@ static int run_until(loopspec_t h, int mode, int n_tokens, const std::vector<int
     // (16, 24) of R = 32, 8 tokens: 109.0 -> 104.5 ms.
     const int gap = mode == MODE_LOOPSPEC ? std::gcd(std::gcd(h->c.d1, h->c.d2), h->c.R) : h->c.R;
     const int seqs = (int)std::count_if(h->prompt_len.begin(), h->prompt_len.end(), [](int n) { return n > 0; });
-    const bool by_event = h->execq[1] && seqs == 1 && gap >= 4;
+    const bool by_event = (h->g.Lp || h->g.Lc) && seqs == 1 && gap >= 4;
+    int r;
+    if (by_event && (r = ensure_quiet_graphs(h))) return r;
+    HIPCHK(h, hipEventRecord(h->ev0, h->st));
     for (;;) {
         HIPCHK(h, hipMemcpyAsync(nc.data(), s.q_ncommit, 4 * Q, hipMemcpyDeviceToHost, h->st));
         HIPCHK(h, hipStreamSynchronize(h->st));
@@ -1244,8 +1251,7 @@ static int run_until(loopspec_t h, int mode, int n_tokens, const std::vector<int
                 if (left > 0) remaining = remaining ? std::min(remaining, left) : left;
             }
         if (!remaining) break;
-        int r = check_err(h);
-        if (r) return r;
+        if ((r = check_err(h))) return r;
         if (by_event) {
             // the quiet steps up to the next readout without the launches that
             // have nothing to do, the step that reads out, and back to the tree
@@ -1270,8 +1276,7 @@ static int run_until(loopspec_t h, int mode, int n_tokens, const std::vector<int
     HIPCHK(h, hipEventRecord(h->ev1, h->st));
     HIPCHK(h, hipEventSynchronize(h->ev1));
     HIPCHK(h, hipEventElapsedTime(&h->last_ms, h->ev0, h->ev1));
-    int r = check_err(h);
-    if (r) return r;
+    if ((r = check_err(h))) return r;
     if (out) {
         std::vector<int32_t> Y((size_t)Q * h->d.max_ctx);
         HIPCHK(h, hipMemcpy(Y.data(), s.Y, Y.size() * 4, hipMemcpyDeviceToHost));
