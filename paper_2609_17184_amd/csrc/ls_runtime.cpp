@@ -566,10 +566,8 @@ int ensure_quiet_graphs(loopspec_t h) {
     return capture_steps(h, kStepsPerGraph, &h->graphq[1], &h->execq[1], true);
 }
 
-int check_err(loopspec_t h) {
-    int32_t e = 0;
-    HIPCHK(h, hipMemcpyAsync(&e, h->sch.err, 4, hipMemcpyDeviceToHost, h->st));
-    HIPCHK(h, hipStreamSynchronize(h->st));
+// The code of a scheduler error word
+int report_err(loopspec_t h, int32_t e) {
     if (e & ERR_NUMERIC) return fail(h, LOOPSPEC_ENUMERIC, "NaN/Inf in readout logits");
     if (e & ERR_CTX) return fail(h, LOOPSPEC_ECAPACITY, "context capacity reached during decoding");
     if (e & ERR_SLOTS) return fail(h, LOOPSPEC_ECAPACITY, "no free branch slot");
@@ -584,6 +582,13 @@ int check_err(loopspec_t h) {
         return fail(h, LOOPSPEC_EHIP, "a wait inside a launch gave up (pass kernel data or sampler shards)");
     }
     return LOOPSPEC_OK;
+}
+
+int check_err(loopspec_t h) {
+    int32_t e = 0;
+    HIPCHK(h, hipMemcpyAsync(&e, h->sch.err, 4, hipMemcpyDeviceToHost, h->st));
+    HIPCHK(h, hipStreamSynchronize(h->st));
+    return report_err(h, e);
 }
 
 int set_mode(loopspec_t h, int mode) {
@@ -764,8 +769,7 @@ int loopspec_create(const loopspec_dims* dims, const loopspec_config* cfg, void*
                              &s.s_c1, &s.s_c2, &s.s_x1, &s.s_x2, &s.s_gate};
     for (auto pp : slot_tabs)
         if ((r = dalloc(h, pp, S))) return r;
-    int32_t** seq_tabs[] = {&s.q_root, &s.q_tdone, &s.q_ncommit, &s.q_target, &s.q_state, &s.q_last_tok,
-                            &s.q_last_src};
+    int32_t** seq_tabs[] = {&s.q_root, &s.q_tdone, &s.q_target, &s.q_state, &s.q_last_tok, &s.q_last_src};
     for (auto pp : seq_tabs)
         if ((r = dalloc(h, pp, d.max_seqs))) return r;
     if ((r = dalloc(h, &s.Y, (size_t)d.max_seqs * d.max_ctx))) return r;
@@ -773,13 +777,15 @@ int loopspec_create(const loopspec_dims* dims, const loopspec_config* cfg, void*
     if ((r = dalloc(h, &s.rowsB, S))) return r;
     if ((r = dalloc(h, &s.rowsC, S))) return r;
     if ((r = dalloc(h, &s.rowsP, S))) return r;
-    if ((r = dalloc(h, &s.nB, 8))) return r;
+    // (what a decode loop asks the scheduler for lies together: one copy)
+    if ((r = dalloc(h, &s.nB, 8 + (size_t)d.max_seqs))) return r;
     s.nC = s.nB + 1;
     s.nP = s.nB + 2;
     s.njc = s.nB + 3;
     s.njs = s.nB + 4;
     s.err = s.nB + 5;
     s.quiet = s.nB + 6;
+    s.q_ncommit = s.nB + 8;
     s.coda_xrow0 = g.Lc ? h->xrow_coda : -1;
     if ((r = dalloc(h, &s.ro_tok, S))) return r;
     if ((r = dalloc(h, &s.ro_aux, S))) return r;
@@ -1222,27 +1228,32 @@ static int start_decode(loopspec_t h, int mode, int n_tokens, std::vector<int>& 
 static int run_until(loopspec_t h, int mode, int n_tokens, const std::vector<int>& nc0, int32_t* out) {
     const int Q = h->d.max_seqs;
     Sched& s = h->sch;
-    std::vector<int32_t> nc(Q);
     long long launched = 0;
     const long long cap = (long long)(n_tokens + 2) * h->c.R * 4 + 64;
     // Models with prelude or coda blocks launch those blocks, the head and the
     // commit with empty lists in every step that reads nothing out: about 27
-    // launches, 75 us of a Raven-shaped step of 850.  Between two readouts the
-    // tree does not change, so the host asks the scheduler how far the next one
-    // is (about 30 us) and replays the short step until then.  A sequence's
+    // launches, 75 us of a Raven-shaped step of 850; 6 launches, 15 us, of a
+    // small model's.  Between two readouts the tree does not change, so the
+    // host asks the scheduler how far the next one is (one copy into pinned
+    // memory, about 10 us) and replays the short step until then.  A sequence's
     // branches start at each other's readouts, so its readouts lie on multiples
-    // of gap = gcd(d1, d2, R) steps; from 4 on three short steps or more pay
-    // for each question.  Several sequences read out at steps of their own,
-    // where asking would gain nothing: they keep the unconditional replay.
-    // (16, 24) of R = 32, 8 tokens: 109.0 -> 104.5 ms.
+    // of gap = gcd(d1, d2, R) steps.  The tokens' speed against whole steps
+    // throughout, widths 192 / 2048 / 5280: gap 2 0.94-0.97 / 0.99 / 1.01, gap 3
+    // 0.99-1.02 / 1.02 / 1.03, gap 4 1.01-1.05 / 1.01-1.03 / 1.04, gap 8 1.12-1.14
+    // / 1.06 / 1.05; without coda blocks, at width 192, 0.99 at gap 4 and 1.12
+    // at 5.  Several sequences read out at steps of their own, where asking
+    // would gain nothing: they keep the unconditional replay.
     const int gap = mode == MODE_LOOPSPEC ? std::gcd(std::gcd(h->c.d1, h->c.d2), h->c.R) : h->c.R;
     const int seqs = (int)std::count_if(h->prompt_len.begin(), h->prompt_len.end(), [](int n) { return n > 0; });
-    const bool by_event = (h->g.Lp || h->g.Lc) && seqs == 1 && gap >= 4;
+    const bool by_event = (h->g.Lp || h->g.Lc) && seqs == 1 && gap >= (h->g.Lc ? 4 : 5);
     int r;
     if (by_event && (r = ensure_quiet_graphs(h))) return r;
+    // row counts, error word, quiet steps and commit counts of the scheduler, in one copy
+    const int32_t* const state = (const int32_t*)h->pin;
+    const int32_t* const nc = state + 8;
     HIPCHK(h, hipEventRecord(h->ev0, h->st));
     for (;;) {
-        HIPCHK(h, hipMemcpyAsync(nc.data(), s.q_ncommit, 4 * Q, hipMemcpyDeviceToHost, h->st));
+        HIPCHK(h, hipMemcpyAsync(h->pin, s.nB, 4 * (8 + (size_t)Q), hipMemcpyDeviceToHost, h->st));
         HIPCHK(h, hipStreamSynchronize(h->st));
         int remaining = 0;
         for (int q = 0; q < Q; ++q)
@@ -1251,13 +1262,11 @@ static int run_until(loopspec_t h, int mode, int n_tokens, const std::vector<int
                 if (left > 0) remaining = remaining ? std::min(remaining, left) : left;
             }
         if (!remaining) break;
-        if ((r = check_err(h))) return r;
+        if ((r = report_err(h, state[s.err - s.nB]))) return r;
         if (by_event) {
             // the quiet steps up to the next readout without the launches that
             // have nothing to do, the step that reads out, and back to the tree
-            int32_t quiet = 0;
-            HIPCHK(h, hipMemcpyAsync(&quiet, s.quiet, 4, hipMemcpyDeviceToHost, h->st));
-            HIPCHK(h, hipStreamSynchronize(h->st));
+            const int quiet = state[s.quiet - s.nB];
             int i = 0;
             for (; i + kStepsPerGraph <= quiet; i += kStepsPerGraph) HIPCHK(h, hipGraphLaunch(h->execq[1], h->st));
             for (; i < quiet; ++i) HIPCHK(h, hipGraphLaunch(h->execq[0], h->st));

@@ -20,8 +20,17 @@ def test_decode_equals_single_steps(R, d1, d2, temperature, Q, second):
     sequence whose depths share a divisor of at least 4 takes the short steps
     (from the smallest such divisor up), others the whole ones; a switch of the
     depths moves the next readout, and the route, between two calls."""
+    check(*model("small_raven", R=R), R, d1, d2, temperature, Q, second)
+
+
+@pytest.mark.parametrize("R,d1", [(8, 4), (10, 5), (12, 6)])
+def test_decode_of_a_model_without_coda_equals_single_steps(R, d1):
+    """Its short steps save fewer launches: from a gap of 5 up."""
+    check(*model("small_raven", R=R, n_coda=0), R, d1, 0, 0.0, 1, None)
+
+
+def check(spec, w, R, d1, d2, temperature, Q, second):
     from paper_2609_17184_amd import Decoder
-    spec, w = model("small_raven", R=R)
     kw = {"temperature": temperature, "top_p": 0.9, "seed": 5} if temperature else {}
     N = 21
     log(f"[quiet] R={R} d1={d1} d2={d2} T={temperature} Q={Q} second={second}")
