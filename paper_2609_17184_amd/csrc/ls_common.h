@@ -169,9 +169,23 @@ __device__ __forceinline__ bool sentinel32(const u32x4& u) {
     const uint32_t a = u[0] > u[1] ? u[0] : u[1], b = u[2] > u[3] ? u[2] : u[3];
     return (a > b ? a : b) == kSentinel;
 }
+// Some element of the first word of N fragments is the sentinel
+template <bool BF16, int N>
+__device__ __forceinline__ bool sentinel_first(const u32x4 (&u)[N]) {
+    u16x2 m = {0, 0};
+    uint32_t f = 0;
+#pragma unroll
+    for (int i = 0; i < N; ++i) {
+        const uint32_t w = u[i][0];
+        if (BF16)
+            m = __builtin_elementwise_max(m, __builtin_bit_cast(u16x2, w));
+        else
+            f = w > f ? w : f;
+    }
+    return BF16 ? __builtin_elementwise_max(m.x, m.y) == 0xFFFFu : f == kSentinel;
+}
 // Some element of N fragments is the sentinel: one running maximum over all of
-// their words and a single test of it (about as many instructions as testing
-// one word of each fragment on its own).
+// their words and a single test of it.
 template <bool BF16, int N>
 __device__ __forceinline__ bool sentinel_any(const u32x4 (&u)[N]) {
     if constexpr (BF16) {

@@ -486,18 +486,52 @@ __device__ __forceinline__ void gemm_finish(const GemmParams& p, int item, int M
 #pragma unroll
     for (int i = 0; i < MAXS; ++i)
         a[i] = buf_load16<COH ? 16 : 0>(ra, i < w.nst ? aoff : kOutOfRange, i * KSTEP * (int)sizeof(WT));
-    if (COH) {
-        // fragments not yet written by their producers are read again, all of
-        // them in the same round (one round trip per round)
-        for (unsigned n = 0;; ++n) {
-            if (!__any(sentinel_any<sizeof(WT) == 2, MAXS>(a)) || poll_abort(n, p.err)) break;
-            bool miss[MAXS];
+    f32x4 acc[1][NMAT];
+    // (steps past the wave's share hold zeros and add exact zeros)
+    auto products = [&]() __attribute__((always_inline)) {
 #pragma unroll
-            for (int i = 0; i < MAXS; ++i) miss[i] = __any(sizeof(WT) == 2 ? sentinel16(a[i]) : sentinel32(a[i]));
+        for (int q = 0; q < NMAT; ++q) acc[0][q] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int i = 0; i < MAXS; ++i) mfma_step<WT, NMAT>(a[i], R.b[i], acc[0]);
+    };
+    if (!COH) {
+        products();
+    } else {
+        // Fragments not yet written by their producers are read again, all of
+        // them in the same round (one round trip per round).  The sentinel is a
+        // NaN and a product with a NaN is one, so once every fragment's first
+        // word has arrived the products themselves are the test of the others:
+        // sums without a NaN used no sentinel.  Only sums with one (data late
+        // in part, or NaN or infinities among it) take the test of every word,
+        // which cost 1.2 % of an Ouro-1.4B decode in front of the products.
+        auto again = [&](const bool (&miss)[MAXS]) __attribute__((always_inline)) {
             __builtin_amdgcn_s_sleep(1);
 #pragma unroll
             for (int i = 0; i < MAXS; ++i)
                 if (miss[i]) a[i] = buf_load16<16>(ra, i < w.nst ? aoff : kOutOfRange, i * KSTEP * (int)sizeof(WT));
+        };
+        for (unsigned n = 0;; ++n) {
+            if (!__any(sentinel_first<sizeof(WT) == 2, MAXS>(a)) || poll_abort(n, p.err)) break;
+            bool miss[MAXS];
+#pragma unroll
+            for (int i = 0; i < MAXS; ++i) miss[i] = __any(sentinel_first<sizeof(WT) == 2, 1>({a[i]}));
+            again(miss);
+        }
+        products();
+        bool nan = false;
+#pragma unroll
+        for (int q = 0; q < NMAT; ++q)
+#pragma unroll
+            for (int v = 0; v < 4; ++v) nan |= acc[0][q][v] != acc[0][q][v];
+        if (__any(nan)) {
+            for (unsigned n = 0;; ++n) {
+                if (!__any(sentinel_any<sizeof(WT) == 2, MAXS>(a)) || poll_abort(n, p.err)) break;
+                bool miss[MAXS];
+#pragma unroll
+                for (int i = 0; i < MAXS; ++i) miss[i] = __any(sizeof(WT) == 2 ? sentinel16(a[i]) : sentinel32(a[i]));
+                again(miss);
+            }
+            products();
         }
 #pragma unroll
         for (int u = 0; u < NSS; ++u) {
@@ -506,12 +540,6 @@ __device__ __forceinline__ void gemm_finish(const GemmParams& p, int item, int M
         }
         if (pre_src && __float_as_uint(pre.x) == kSentinel) pre.x = poll_f32(pre_src, p.err);
     }
-    f32x4 acc[1][NMAT];
-#pragma unroll
-    for (int q = 0; q < NMAT; ++q) acc[0][q] = f32x4{0.f, 0.f, 0.f, 0.f};
-    // steps past the wave's share hold zeros and add exact zeros
-#pragma unroll
-    for (int i = 0; i < MAXS; ++i) mfma_step<WT, NMAT>(a[i], R.b[i], acc[0]);
     gemm_epilogue<WT, EPI, NMAT, 1, NSS, COH>(p, item, M, w, acc, ssv, smem, has_pre, pre, kgi);
 }
 

@@ -173,3 +173,26 @@ def test_prefill_again_mid_decode():
         one.close()
     assert np.array_equal(np.concatenate([first[0], second[0]]), ref["a"])
     assert np.array_equal(second[1], ref["c"])
+
+
+@pytest.mark.parametrize("name", ["small_bf16", "tiny"])
+def test_non_finite_rows_end_the_pass(name):
+    """Infinities and NaN inside the persistent pass are data, not data that is late: the call reports them, and the
+    handle reads out the next sequence as before."""
+    spec, w = model(name, tied_head=False)
+    w = dict(w)
+    w["embed"] = w["embed"].copy()
+    bad = 7
+    w["embed"][bad] = 0x7F00 if w["embed"].dtype == np.uint16 else 1e38      # 1.7e38: infinite once rounded or squared
+    dec = Decoder(spec, w, R=spec.R, d1=1, d2=2, max_seqs=1, max_ctx=64)
+    pr = [t for t in prompt(spec, 12) if t != bad]
+    dec.prefill(0, pr)
+    want, _ = dec.forced_readout(0, [3, 4])
+    log(f"[edges] {name}: a non-finite row")
+    with pytest.raises(B.LoopSpecError) as e:
+        dec.forced_readout(0, [bad, 4])
+    assert e.value.code == B.ENUMERIC
+    dec.rewind(0)
+    got, _ = dec.forced_readout(0, [3, 4])
+    assert np.array_equal(got, want)
+    dec.close()
