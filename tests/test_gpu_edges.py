@@ -183,7 +183,7 @@ def test_non_finite_rows_end_the_pass(name):
     w = dict(w)
     w["embed"] = w["embed"].copy()
     bad = 7
-    w["embed"][bad] = 0x7F00 if w["embed"].dtype == np.uint16 else 1e38      # 1.7e38: infinite once rounded or squared
+    w["embed"][bad] = 0x7F80 if w["embed"].dtype == np.uint16 else np.inf
     dec = Decoder(spec, w, R=spec.R, d1=1, d2=2, max_seqs=1, max_ctx=64)
     pr = [t for t in prompt(spec, 12) if t != bad]
     dec.prefill(0, pr)
