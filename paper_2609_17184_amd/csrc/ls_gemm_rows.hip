@@ -9,23 +9,19 @@
 // A workgroup is four waves that split k, for FT feature tiles (of each
 // matrix) and all rows; each wave loads both operands straight into
 // registers, PF steps ahead, with no barrier until the partials meet in LDS,
-// where they are summed in wave order.  Under load
-// a weight fragment takes 3.4 us to arrive, so it is the bytes in flight that
-// set the rate: launches whose workgroups would leave registers idle (DEEP, see
-// launch_nt) load further ahead, the more so for passes of at most two live
-// row tiles (loads return in order, so the activations are held as long as the
-// weights).  Row tiles past the live ones are neither
+// where they are summed in wave order.  Row tiles past the live ones are neither
 // read nor multiplied.  A row's result depends on nothing but its own values:
 // the split of k is fixed by K, and every row tile is summed in the same order
 // whatever the depth.
 //
-// Measured (us per launch, TB/s of weights; before: stream-K with row-major
-// activations, the 64-row LDS tiles for O and at h = 2048).  Raven width, 24
-// rows: gate/up 114 -> 64 (5.9), QKV 86 -> 33 (5.1), down 120 -> 55 (3.5), O
-// 50 -> 18 (3.1), LM head 179 -> 109 (6.4).  h = 2048, 16 rows: QKV 29 -> 9.2,
-// gate/up 37 -> 12.3, O and down 24 -> 9.9 on average.  Bound by HBM and the
-// loads in flight; down (330 workgroups for 256 CUs, 140 steps each) and O by
-// the ragged last CUs.
+// Measured by kernel trace inside a decode, us per launch (TB/s of weights).
+// Raven width, 8 live rows / 24 / 48: QKV 29 (5.7) / 35 (4.8) / 46, O 16 (3.4) /
+// 21 (2.6) / 28, gate/up 62 (6.1) / 77 (4.9) / 108, down 48 (3.9) / 63 (3.0) / 80,
+// LM head at 8 to 24 rows 108 (6.4).  h = 2048, F = 5120, 24 / 48: QKV 11.4 / 15.5,
+// O 6.6 / 8.3, gate/up 14.2 / 17.0, down 11.4 / 14.9.  Bound by HBM and the
+// loads in flight (a weight fragment takes 3.4 us to arrive under load); down
+// and O (330 workgroups for 256 CUs) by the ragged last CUs; past 32 rows by the
+// activations, four fragments for one or two of weights.
 #include "ls_opd_dev.h"
 
 namespace ls {
@@ -89,10 +85,8 @@ __device__ __forceinline__ void rows_stream(const __amdgpu_buffer_rsrc_t (&rw)[F
     }
 }
 
-// k steps ahead for NT row tiles and W weight fragments per step
-constexpr int rows_depth(bool deep, int nt, int w) {
-    return !deep ? (nt <= 2 ? 6 : 4) : nt <= 2 ? (w == 1 ? 16 : 10) : (w == 1 ? 8 : 6);
-}
+// k steps ahead for NT live row tiles
+constexpr int rows_depth(bool deep, int nt) { return nt <= 2 || deep ? 6 : 4; }
 
 template <typename WT, int EPI, int NMAT, int FT, int NT, bool DEEP>
 __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) k_gemm_rows(GemmParams p) {
@@ -157,9 +151,9 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) k
     };
     float* const mine = part + (size_t)wv * ROWS * LD;
     if (NT == 2 || ntl <= 2)
-        rows_stream<WT, NMAT, FT, 2, rows_depth(DEEP, 2, FT * NMAT), LD>(rw, ra, ns, k0, n, ntl, mine, between);
+        rows_stream<WT, NMAT, FT, 2, rows_depth(DEEP, 2), LD>(rw, ra, ns, k0, n, ntl, mine, between);
     else
-        rows_stream<WT, NMAT, FT, NT, rows_depth(DEEP, NT, FT * NMAT), LD>(rw, ra, ns, k0, n, ntl, mine, between);
+        rows_stream<WT, NMAT, FT, NT, rows_depth(DEEP, NT), LD>(rw, ra, ns, k0, n, ntl, mine, between);
     __syncthreads();
     auto sum = [&](int row, int col) {
         f32x4 v = *(const f32x4*)(part + (size_t)row * LD + col);
@@ -258,15 +252,22 @@ template <typename WT, int EPI, int NMAT, int FT, int NT>
 static hipError_t launch_ft(const GemmParams& p, hipStream_t st) {
     GemmParams q = p;
     void* args[] = {(void*)&q};
-    // Deep loads where the workgroups fill every CU once but at most the two
-    // places that the deep variant leaves, and a wave's share of k is a few
-    // times its depth.  Raven width at 24 rows: down 59 -> 45 us, QKV 36 -> 33;
-    // with more workgroups the third one per CU is worth more (gate/up 71 us
-    // against 73 deep, LM head 120 against 125), with shorter shares the first
-    // loads are (QKV at h = 2048: 9.2 us against 13.2).
+    // Gate/up reads two weight fragments a step and so has the most to gain
+    // from six steps ahead instead of four behind more than two row tiles
+    // (two row tiles always have six), at the registers of the third workgroup
+    // of a CU.  33 to 64 live rows, fp16, workgroups / k steps: 130 / 64 13.2 ->
+    // 10.2 us, 272 / 64 19.0 -> 16.7, 384 / 128 43.7 -> 35.8, 480 / 192 63.8 -> 53.7;
+    // up to 32 rows the same time.  Past 512 workgroups those rows miss the
+    // third one (770 / 128: 47.6 -> 48.0 us at 24 rows, 65.3 -> 56.9 at 40), and with
+    // shorter shares the first loads weigh more (276 / 48: 16.1 -> 17.2).  fp32
+    // steps hold half of the columns: 272 / 96 27.0 -> 27.7 us, 304 / 128 34.2 ->
+    // 36.8, 368 / 176 48.2 -> 44.2, 432 / 256 80.3 -> 78.7.  (QKV, O and down lose
+    // up to 7 % so and gain at most 5 %; 10 or 16 steps ahead for two row tiles lose 10 %
+    // of all of them.)
     const int wgs = (p.tiles + FT - 1) / FT, ns = p.K / WTraits<WT>::KSTEP;
-    const void* f = wgs >= 256 && wgs <= 512 && ns >= 160 ? (const void*)k_gemm_rows<WT, EPI, NMAT, FT, NT, true>
-                                                          : (const void*)k_gemm_rows<WT, EPI, NMAT, FT, NT, false>;
+    const void* f = (const void*)k_gemm_rows<WT, EPI, NMAT, FT, NT, false>;
+    if constexpr (NMAT == 2 && NT == 4)
+        if (wgs <= 512 && ns >= (sizeof(WT) == 2 ? 64 : 160)) f = (const void*)k_gemm_rows<WT, EPI, NMAT, FT, NT, true>;
     return ls_launch(f, dim3(wgs), dim3(256), args, 0, st);
 }
 
