@@ -46,6 +46,17 @@ def shaped(spec, noise, wv, wo):
     return w, put
 
 
+def near_model(spec, nats=8.0):
+    """Scores of `nats` times the mean cosine of RoPE's angles: near keys weigh most, by a power of the distance."""
+    w, put = shaped(spec, noise=0.1, wv=0.15, wo=0.15)
+    for name in list(w):
+        if name.rsplit(".", 1)[-1] in ("wq", "wk"):
+            a = f32(w, name)
+            a[:, 0] = np.sqrt(nats / (np.sqrt(spec.head_dim) * spec.hidden))
+            put(name, a)
+    return w
+
+
 SINK_NATS = 18.0
 
 
@@ -72,6 +83,10 @@ def sink_model(spec):
                 a[:, 0 if kind == "wq" else 1] = s * ramp
             put(name, a)
     return w
+
+
+def near_spec(H=1, dh=96, F=512, V=800):
+    return synth.ModelSpec(H * dh, H, dh, F, V, 0, 1, 0, R=2, alpha=0.3)
 
 
 def sink_spec(H=2, dh=96):

@@ -11,7 +11,7 @@ import synth
 from gpu_common import MARGIN, TOL, log, model, oracle_lm, prompt
 from oracle import model as OM
 from paper_2609_17184_amd import Decoder
-from prompt_models import REL, SINK_NATS, readouts, rel, sink_model, sink_prompt, sink_spec
+from prompt_models import REL, SINK_NATS, near_model, near_spec, readouts, rel, sink_model, sink_prompt, sink_spec
 
 pytestmark = pytest.mark.gpu
 
@@ -46,7 +46,8 @@ def test_prompt_lengths(name, n):
 
 @pytest.mark.parametrize("n", [2048, 2049, 2111])
 def test_prompt_of_several_passes(n):
-    """A pass holds 2048 positions: the next one reads the first one's keys and values."""
+    """A pass holds 2048 positions, the next one goes on behind them, in prelude and coda blocks too.  (Each key weighs
+    little in this model; test_prompt_near_keys sees what the second pass does.)"""
     spec, w = model("small_raven", R=2)
     check(spec, w, oracle_lm("small_raven", R=2), n, 2200)
 
@@ -69,7 +70,8 @@ def test_prompt_head_sizes(dh, n):
 
 
 def test_prompt_of_many_query_blocks():
-    """32 queries per wave from 256 blocks of 128 on: 2100 positions of 16 heads, keys of 33 tiles, two passes."""
+    """32 queries per wave from 256 blocks of 128 on: 2100 positions of 16 heads, keys of 33 tiles, two passes.  (As
+    above: single keys weigh little here.)"""
     spec = synth.ModelSpec(256, 16, 16, 256, 304, 0, 1, 0, R=2, alpha=0.3)
     w = synth.make_weights(spec, seed=0)
     check(spec, w, OM.LoopedLM(spec, w), 2100, 2200)
@@ -93,3 +95,12 @@ def test_prompt_small_weights(dh):
     score of SINK_NATS is a sum of products of two factors rounded at 2^-11 each."""
     spec = sink_spec(dh=dh)
     assert off(spec, sink_model(spec), sink_prompt(spec), 5, 200) < REL + 2 * SINK_NATS * 2.0 ** -11
+
+
+@pytest.mark.parametrize("H,dh,n", [(1, 96, 2049), (1, 96, 2060), (1, 96, 2111), (16, 16, 2111), (32, 96, 1000), (32, 96, 1024)])
+def test_prompt_near_keys(H, dh, n):
+    """Readouts that hang on the keys just before them, so on every position of a second pass and on its
+    view of the first; and 32 queries per wave for heads of 16 and 96 (256 blocks of 128, the last one ragged or full)."""
+    spec = near_spec(H, dh, V=800 if H == 1 else 304)
+    pr = [int(t) for t in np.random.default_rng(n).integers(0, spec.vocab, n)]
+    assert off(spec, near_model(spec), pr, 5, n + 32) < REL
