@@ -5,7 +5,6 @@
 namespace ls {
 
 enum Epi { EPI_QKV = 0, EPI_RESID = 1, EPI_SWIGLU = 2, EPI_LOGITS = 3 };
-enum AMode { A_NORM = 0, A_BUF = 1 };
 
 // k steps (one 16-byte weight load per lane each) a wavefront of the direct
 // path keeps in flight for an epilogue kind (register budget: the residual

@@ -87,6 +87,8 @@ __device__ __forceinline__ WaveGeo wave_geo(const GemmParams& p, int item, int k
 }
 
 // Buffer resource over [p, p + bytes): loads at offsets >= bytes return zero.
+// The scalar operand counts towards the offset and saturates (measured on
+// gfx950: with a range of 4096, scalar offsets from 4096 to 4 MB read nothing).
 constexpr int kOutOfRange = (int)0x80000000u;   // a lane offset beyond every resource
 __device__ __forceinline__ __amdgpu_buffer_rsrc_t buf_rsrc(const void* p, uint32_t bytes) {
     return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p), (short)0, (int)bytes, 0x00020000);
@@ -190,14 +192,13 @@ __device__ __forceinline__ void gemm_load_b_staged(const GemmParams& p, int item
 // finishes the tile as if they were kg slices of one workgroup, so the sum
 // order is fixed: slices within a workgroup, then workgroups in order.  The
 // other workgroups end here.
-template <typename WT, int EPI, int NMAT, int NTM, int NSS, bool COH = false>
+template <typename WT, int EPI, int NMAT, int NSS, bool COH = false>
 __device__ __forceinline__ void gemm_epilogue(const GemmParams& p, int item, int M, const WaveGeo& w,
-                                              f32x4 (&acc)[NTM][NMAT], const float (&ssv)[NSS], char* smem,
+                                              const f32x4 (&acc)[NMAT], const float (&ssv)[NSS], char* smem,
                                               bool has_pre = false, float2 pre = float2{0.f, 0.f}, int kgi = 0) {
     constexpr bool BF = sizeof(WT) == 2;
     constexpr bool norm = EPI != EPI_RESID;
     const int tid = tid_local(), nwaves = blockDim.x >> 6;
-    const int nt = COH ? 1 : (M + 15) >> 4;             // the pass holds at most 16 rows
     const int tiles_h = p.g.ssq_tiles;
     float* rinv = (float*)smem;                              // [64]
     if (norm) {
@@ -218,18 +219,15 @@ __device__ __forceinline__ void gemm_epilogue(const GemmParams& p, int item, int
     }
     // (every wave is past the previous epilogue's reads of the partials)
     __syncthreads();
-    const int plane = nt * 16 * 16;                     // one tile's M x 16 block
+    constexpr int plane = 256;                          // one tile's 16 x 16 block
     float* red = (float*)(smem + 256);                  // [tpw][ks][NMAT][plane]
     if (w.tile_ok) {
 #pragma unroll
-        for (int q = 0; q < NMAT; ++q)
+        for (int q = 0; q < NMAT; ++q) {
+            float* d = red + ((size_t)(w.tl * p.ks + w.ksl) * NMAT + q) * plane;
 #pragma unroll
-            for (int rt = 0; rt < NTM; ++rt) {
-                if (rt >= nt) break;
-                float* d = red + ((size_t)(w.tl * p.ks + w.ksl) * NMAT + q) * plane;
-#pragma unroll
-                for (int v = 0; v < 4; ++v) d[(rt * 16 + w.grp * 4 + v) * 16 + w.j] = acc[rt][q][v];
-            }
+            for (int v = 0; v < 4; ++v) d[(w.grp * 4 + v) * 16 + w.j] = acc[q][v];
+        }
     }
     __syncthreads();
     int nsl = p.ks;                                     // slices the finish sums, in order
@@ -486,13 +484,13 @@ __device__ __forceinline__ void gemm_finish(const GemmParams& p, int item, int M
 #pragma unroll
     for (int i = 0; i < MAXS; ++i)
         a[i] = buf_load16<COH ? 16 : 0>(ra, i < w.nst ? aoff : kOutOfRange, i * KSTEP * (int)sizeof(WT));
-    f32x4 acc[1][NMAT];
+    f32x4 acc[NMAT];
     // (steps past the wave's share hold zeros and add exact zeros)
     auto products = [&]() __attribute__((always_inline)) {
 #pragma unroll
-        for (int q = 0; q < NMAT; ++q) acc[0][q] = f32x4{0.f, 0.f, 0.f, 0.f};
+        for (int q = 0; q < NMAT; ++q) acc[q] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-        for (int i = 0; i < MAXS; ++i) mfma_step<WT, NMAT>(a[i], R.b[i], acc[0]);
+        for (int i = 0; i < MAXS; ++i) mfma_step<WT, NMAT>(a[i], R.b[i], acc);
     };
     if (!COH) {
         products();
@@ -522,7 +520,7 @@ __device__ __forceinline__ void gemm_finish(const GemmParams& p, int item, int M
 #pragma unroll
         for (int q = 0; q < NMAT; ++q)
 #pragma unroll
-            for (int v = 0; v < 4; ++v) nan |= acc[0][q][v] != acc[0][q][v];
+            for (int v = 0; v < 4; ++v) nan |= acc[q][v] != acc[q][v];
         if (__any(nan)) {
             for (unsigned n = 0;; ++n) {
                 if (!__any(sentinel_any<sizeof(WT) == 2, MAXS>(a)) || poll_abort(n, p.err)) break;
@@ -540,7 +538,7 @@ __device__ __forceinline__ void gemm_finish(const GemmParams& p, int item, int M
         }
         if (pre_src && __float_as_uint(pre.x) == kSentinel) pre.x = poll_f32(pre_src, p.err);
     }
-    gemm_epilogue<WT, EPI, NMAT, 1, NSS, COH>(p, item, M, w, acc, ssv, smem, has_pre, pre, kgi);
+    gemm_epilogue<WT, EPI, NMAT, NSS, COH>(p, item, M, w, acc, ssv, smem, has_pre, pre, kgi);
 }
 
 // Standalone direct path (<= 16 rows, no exchange within the launch): the
@@ -617,12 +615,12 @@ __device__ __forceinline__ void gemm_direct(const GemmParams& p, int item, int k
     __builtin_amdgcn_sched_barrier(0);
     // (5) MFMAs over the fragments in step order; steps past the wave's share
     //     hold zeros and add exact zeros
-    f32x4 acc[1][NMAT];
+    f32x4 acc[NMAT];
 #pragma unroll
-    for (int q = 0; q < NMAT; ++q) acc[0][q] = f32x4{0.f, 0.f, 0.f, 0.f};
+    for (int q = 0; q < NMAT; ++q) acc[q] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-    for (int i = 0; i < MAXS; ++i) mfma_step<WT, NMAT>(a[i], R.b[i], acc[0]);
-    gemm_epilogue<WT, EPI, NMAT, 1, NSS, false>(p, item, M, w, acc, ssv, smem, has_pre, pre, kgi);
+    for (int i = 0; i < MAXS; ++i) mfma_step<WT, NMAT>(a[i], R.b[i], acc);
+    gemm_epilogue<WT, EPI, NMAT, NSS, false>(p, item, M, w, acc, ssv, smem, has_pre, pre, kgi);
 }
 
 }  // namespace ls

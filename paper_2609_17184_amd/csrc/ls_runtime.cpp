@@ -591,12 +591,6 @@ int check_err(loopspec_t h) {
     return report_err(h, e);
 }
 
-int set_mode(loopspec_t h, int mode) {
-    HIPCHK(h, hipMemcpyAsync(h->mode, &mode, 4, hipMemcpyHostToDevice, h->st));
-    HIPCHK(h, hipStreamSynchronize(h->st));
-    return LOOPSPEC_OK;
-}
-
 }  // namespace
 
 // ===========================================================================

@@ -513,22 +513,10 @@ __device__ __forceinline__ void commit_job(const Sched& s, int j, int t, int kv,
     }
 }
 
-__global__ void __launch_bounds__(256) k_kv_commit(Sched s, char* kvc, const char* kvs, int wbytes) {
-    const int j = blockIdx.y;
-    if (j >= *s.njc) return;
-    commit_job(s, j, blockIdx.x >> 1, blockIdx.x & 1, kvc, kvs, wbytes);
-}
-
-hipError_t launch_kv_commit(const Sched& s, void* kvc, const void* kvs, int wbytes, hipStream_t st) {
-    hipLaunchKernelGGL(k_kv_commit, dim3(s.g.T * 2, s.max_seqs), dim3(256), 0, st, s, (char*)kvc,
-                       (const char*)kvs, wbytes);
-    return hipGetLastError();
-}
-
 // The two independent tails of a decode step in one launch: rows y <
-// max_seqs of the grid copy the committed roots' keys and values (as
-// k_kv_commit), row y = max_seqs embeds the spawned branches' tokens (as
-// k_embed); x covers max(2 T, slots).
+// max_seqs of the grid copy the committed roots' keys and values, row y =
+// max_seqs embeds the spawned branches' tokens (as k_embed); x covers
+// max(2 T, slots).
 template <typename WT>
 __global__ void __launch_bounds__(256) k_commit_embed(Sched s, char* kvc, const char* kvs, int wbytes, const WT* E,
                                                       float* X) {

@@ -8,7 +8,7 @@ produced -- and at every shallower depth by recomputation, and the logits are
 compared with the oracle's readout of the same prefix at the same depth: the
 first proposal's q1 = C(H^(d1)) and the gate's q2~ = C(H^(d2)) in particular
 (Alg. 1; Sec. 4.2-4.3).  The launch configurations covered are the persistent
-pass (<= 16 slots), the 64-row per-kernel path (more than 16 slots), the
+pass (<= 16 slots), the per-kernel path of more than 16 slots, the
 per-kernel attention over more than 32 chunks of 64 positions, the
 shared-prefix task attention, and a model with prelude and coda blocks.  Also: one vanilla token per call equals the
 vanilla decode."""
@@ -67,11 +67,11 @@ def _check_tree(dec, spec, lm, pr, d1, d2, cache, what, coda=False):
 
 @pytest.mark.parametrize("name,n_prompt,max_slots,max_ctx,per_kernel,d1,d2,shared", [
     ("small_bf16", 70, 0, 256, False, 1, 2, False),      # persistent pass (<= 16 slots)
-    ("small_bf16", 70, 24, 256, False, 1, 2, False),     # 64-row per-kernel path
+    ("small_bf16", 70, 24, 256, False, 1, 2, False),     # per-kernel path of more than 16 slots
     ("small_bf16", 1100, 0, 2600, True, 1, 2, False),    # per-kernel attention over 41 chunks
-    ("small_bf16", 1100, 24, 2600, False, 1, 2, False),  # 64-row path, long context
+    ("small_bf16", 1100, 24, 2600, False, 1, 2, False),  # the same, long context
     ("small_bf16", 1100, 0, 2600, True, 1, 2, True),     # shared-prefix task attention
-    ("small_bf16", 70, 24, 256, False, 1, 2, True),      # shared-prefix, 64-row path
+    ("small_bf16", 70, 24, 256, False, 1, 2, True),      # shared-prefix, more than 16 slots
     ("tiny", 32, 0, 256, False, 1, 3, False),            # fp32 model
     ("tiny", 32, 0, 256, True, 1, 3, True),              # fp32, shared-prefix
 ])

@@ -126,7 +126,7 @@ def test_batch_invariance_across_sequences(Q, max_ctx):
     alone or batched with other sequences (other rows, another M every step).
     Q = 2 keeps the (4, 1, 2) slot pool at 14 rows (persistent pass kernel;
     with max_ctx 2600 its chunk-task attention); Q = 3 needs 21 (per-kernel
-    launches with 64-row tiles)."""
+    launches of the 17-to-64-row weight stream)."""
     name = "small_bf16"
     spec, w = model(name)
     from paper_2609_17184_amd import Decoder

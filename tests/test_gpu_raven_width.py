@@ -4,13 +4,12 @@ Hidden 5280 (55 heads of 96), FFN 17920, vocabulary 65536, bf16: the widths
 of the benchmarked prelude / core / coda model, with one block per stack and
 R = 4 so that the fp64 oracle stays within seconds.  Every decode GEMM of
 this width streams K = 5280 or 17920 in more k steps than one wave holds,
-so the weight stream is split over several workgroups per output tile; the
+so its k range is split over several waves per output tile; the
 test checks the readout logits at every depth (teacher-forced along the
 oracle's greedy trajectory) and the first token after prefill, with a branch
-pool of at most 16 slots (16-row stream-K launches), of 24 (32-row launches)
-and of 64 (64-row launches): at this width the QKV, gate/up, down and LM-head
-launches of more than 16 rows stream their weights stream-K too, the O
-projection takes the 64-row tiles.  Prefill runs 64-row launches.
+pool of at most 16 slots (stream-K launches), of 24 and of 64 (the 32- and
+64-row instantiations of the weight stream of 17 to 64 rows, one row live).
+The prompt runs in one prompt pass, its last position as a single row.
 Sec. 3.1 (Eq. loop-recurrence), Fig. 2."""
 import numpy as np
 import pytest
