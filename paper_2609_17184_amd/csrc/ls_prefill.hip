@@ -26,14 +26,16 @@
 // and loads both operands straight into registers: no LDS and no barrier
 // until the partials meet.
 //
-// Measured (h = 2048, F = 5632, us per launch, and the rate): QKV 25.5 (505
-// TFLOP/s), O 9.8 (440), gate/up 47.6 (497) and down 19.1 (617) at 512 rows;
-// 66.7 (772), 26.7 (645), 126.5 (747) and 52.7 (897) at 2048, of the 2100 that
-// back-to-back MFMAs reach.  The decode's 64-row launches took eight times 30,
-// 18, 38 and 32 us for 512 rows.  What bounds them now: the CU's L1 (64 B a
-// clock, both operands once per workgroup and the weights once more for the
-// second row half), and at 512 rows the first loads and the epilogue, about 6
-// us of a launch.
+// Measured by kernel trace inside a prompt (us per launch, and the rate in
+// TFLOP/s).  h = 2048, F = 5632, 512 rows: QKV 31 (415), O 12.6 (340), gate/up 48
+// (490), down 25 (465); 2048 rows: 75 (685), 31 (560), 131 (720), 65 (725).  h = 5280,
+// F = 17920, 320 rows: 110 (485), 45 (400), 212 (570), 133 (455); 1024 rows: 230
+// (745), 107 (535), 485 (800), 313 (620).  Back-to-back MFMAs reach 2100; the
+// decode's 64-row launches took eight times 30, 18, 38 and 32 us for 512 rows of
+// the first shape.  What bounds them now: the CU's L1 (64 B a clock, both
+// operands once per workgroup and the weights once more for the second row
+// half), and at 512 rows the weights' way from HBM, the first loads and the
+// epilogue.
 #include "ls_prefill.h"
 
 #include <algorithm>
@@ -359,11 +361,14 @@ static_assert(3 * 16 * 1024 <= 128 * 132 * 4, "staging buffers fit the partials'
 template <typename WT, int EPI, int NMAT>
 static hipError_t launch_shape(const PrefillGemm& p, hipStream_t st) {
     const int tb = ((p.tiles * NMAT + 7) / 8) * ((p.M + 127) / 128), sb = ((p.tiles * NMAT + 3) / 4) * ((p.M + 63) / 64);
-    // Tiles of 128 x 128 once there is one for every CU: at 2048 rows they take
-    // 26.7 us against 47.7 in slices (O, 256 tiles) and 66.7 against 147.7 (QKV,
-    // 768); at 192 tiles (QKV, 512 rows) slices are faster, 25.5 us against 28.6,
-    // and at 64 (O, 512 rows) 9.8 against 22.0 (h = 2048).
-    const bool tile = tb >= 256;
+    // Slices fill the CUs with a quarter of the work per workgroup, tiles read
+    // half as much per flop.  us per launch inside a prompt (h = 2048, F = 5632),
+    // tiles / slices, at so many tiles: 48 QKV 31 / 15; 128 O 27 / 21, down 60 / 45;
+    // 192 QKV 31 / 30, O 29 / 34, down 62 / 71; 208 to 240 O
+    // 30 / 48, down 64 / 105, QKV 31 / 37; from 256 on tiles win by 1.2 to 2.  fp32
+    // (a quarter of the arithmetic rate, so the chip's idle part weighs more):
+    // 192 gate/up 80 / 62, 216 QKV 79 / 90, 256 gate/up 81 / 90, 264 QKV 136 / 110.
+    const bool tile = tb >= (sizeof(WT) == 2 ? 200 : 256);
     const void* f = tile ? (const void*)k_prefill_tile<WT, EPI, NMAT> : (const void*)k_prefill_slice<WT, EPI, NMAT>;
     PrefillGemm q = p;
     void* args[] = {(void*)&q};
@@ -394,12 +399,17 @@ static hipError_t launch_shape(const PrefillGemm& p, hipStream_t st) {
 // values are read from memory once per workgroup, not once per row, and the
 // next tile's loads are in flight under the current one's products.
 //
-// Measured (16 heads x 128, us per launch): 14.9 at 512 positions, 73 at 2048
-// (234 TFLOP/s of the causal products), 206 for 2048 rows behind 3952
-// positions (405); one workgroup per (row, head), the decode's arrangement,
-// took 145, 1190 and 4240.  What bounds it: the exponentials and the packing
-// of the weights (VALU) next to the two products, and at 512 positions the
-// 128 workgroups of 16 queries per wave, one on every other CU.
+// Measured (16 heads x 128, us per launch): 14.3 at 512 positions, 61 at 2048
+// (280 TFLOP/s of the causal products), 202 for 2048 rows behind 4096 positions
+// (425); one workgroup per (row, head), the decode's arrangement, took 145,
+// 1190 and 4240.  What bounds it: the exponentials and the packing of the
+// weights (VALU) next to the two products, and at 512 positions the 128
+// workgroups, one on every other CU.
+//
+// A masked key of a loaded tile has the weight 0, and 0 times an infinite
+// value is NaN: a position that is not finite makes the rows of its key tile
+// before it so too.  (The last position of such a prompt is not finite either
+// way, and the call fails.)
 // ---------------------------------------------------------------------------
 template <int DH, int NQ>
 __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) k_prefill_attn(PrefillAttn p) {
@@ -575,9 +585,14 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) k
 
 template <int DH>
 static hipError_t launch_attn_dh(const PrefillAttn& p, hipStream_t st) {
-    // 32 queries per wave read each key tile half as often; 16 where that would leave CUs idle
+    // 32 queries per wave read each key tile half as often but leave half the
+    // workgroups: they pay where those still are three per CU and the keys go
+    // far back.  us per launch, 32 / 16 queries, 2048 rows behind 0 / 4096 / 8192
+    // positions: 55 heads of 96 (880 workgroups of 128 queries) 137 / 137, 415 / 435,
+    // 666 / 728; 16 heads of 128 (256) 66 / 64, 204 / 202, 310 / 304; 16 of 64 47 / 42,
+    // 133 / 125, 219 / 198; 8 of 96 (128) 56 / 40, 155 / 112, 253 / 183.
     const int n2 = p.g.H * ((p.M + 127) / 128), n1 = p.g.H * ((p.M + 63) / 64);
-    if (n2 >= 256)
+    if (n2 >= 768 && p.p0 >= 4096)
         hipLaunchKernelGGL((k_prefill_attn<DH, 2>), dim3(n2), dim3(256), 0, st, p);
     else
         hipLaunchKernelGGL((k_prefill_attn<DH, 1>), dim3(n1), dim3(256), 0, st, p);

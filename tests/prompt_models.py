@@ -104,3 +104,42 @@ def readouts(lm, pr, tok, node=None):
 
 def rel(a, b):
     return np.linalg.norm(a - b, axis=-1) / np.linalg.norm(b, axis=-1)
+
+
+def readouts64(spec, w, ids):
+    """The oracle's readouts [R, V] of the last of `ids`, for prompts too long for it: the same forward pass in float64
+    on the GPU (core blocks only)."""
+    import torch
+
+    def t(name):
+        a = w[name]
+        return torch.from_numpy(synth.bf16_bits_to_f32(a) if a.dtype == np.uint16 else a).cuda().double()
+
+    def norm(x, g):
+        return x * torch.rsqrt((x * x).mean(-1, keepdim=True) + spec.rms_eps) * t(g)
+
+    H, dh, T = spec.n_heads, spec.head_dim, len(ids)
+    pos = torch.arange(T, device="cuda")
+    ang = pos[:, None].double() * spec.rope_base ** (-2.0 * torch.arange(dh // 2, device="cuda").double() / dh)
+    c, s = ang.cos()[:, None], ang.sin()[:, None]
+
+    def rope(x):
+        a, b = x[..., :dh // 2], x[..., dh // 2:]
+        return torch.cat([a * c - b * s, b * c + a * s], -1)
+
+    x, out = t("embed")[torch.as_tensor(np.asarray(ids)).long().cuda()], []
+    for _ in range(spec.R):
+        for i in range(spec.n_core):
+            n = norm(x, f"core.{i}.attn_norm")
+            q, k, v = ((n @ t(f"core.{i}.{m}").T).view(T, H, dh) for m in ("wq", "wk", "wv"))
+            q, k, a = rope(q), rope(k), torch.empty_like(v)
+            for h in range(H):
+                kt, vh = k[:, h].T.contiguous(), v[:, h].contiguous()
+                for r in range(0, T, 1024):
+                    z = q[r:r + 1024, h].contiguous() @ kt / np.sqrt(dh)
+                    a[r:r + 1024, h] = z.masked_fill(pos[None] > pos[r:r + 1024, None], -np.inf).softmax(-1) @ vh
+            x = x + a.reshape(T, -1) @ t(f"core.{i}.wo").T
+            n = norm(x, f"core.{i}.ffn_norm")
+            x = x + (torch.nn.functional.silu(n @ t(f"core.{i}.wg").T) * (n @ t(f"core.{i}.wu").T)) @ t(f"core.{i}.wd").T
+        out.append(norm(x[-1], "final_norm") @ t("head").T)
+    return torch.stack(out).cpu().numpy()
