@@ -833,8 +833,8 @@ hipError_t launch_zero_words(unsigned long long* p, size_t n, hipStream_t st) {
 // is bound by latency; with a launch per role and 64 rows, 12 launches for 256
 // rows, every chain also waited for the slowest row of its launch three times
 // and the chip drained in between, and no row's loads ran under another's
-// chain.  The whole call, 4 rows of V = 4096: 113 -> 85 us; 256 rows of 65536
-// with top-p 0.95: 1023 -> 974 us, where the arithmetic of the races and the
+// chain.  The whole call, 4 rows of V = 4096: 113 -> 84 us (40 of them the
+// kernel); 256 rows of 65536 with top-p 0.95: 1023 -> 970 us (915), where the arithmetic of the races and the
 // histogram atomics of four workgroups per CU take over from the barriers.
 // ---------------------------------------------------------------------------
 struct CascadeArgs {
@@ -879,7 +879,11 @@ __global__ void __launch_bounds__(kSThreads) __attribute__((amdgpu_waves_per_eu(
             if (k == 1 && !a.has_second) continue;
             // (opaque: what depends on the thread's ids alone, the first Philox
             // products among it, is not held in registers across the roles)
-            // (163 registers at E = 16 before the bound of four workgroups a CU, 251 without it)
+            // (163 registers at E = 16, 251 without this; the bound of four
+            // workgroups a CU then costs 19 registers spilled at E = 16, 80
+            // bytes a lane, and one at E = 12; 256 rows of 65536 ids with top-p
+            // 0.95 take 971 us so and 1112 with three, 64 rows 209 and 268
+            // without top-p)
             asm volatile("" : "+v"(c.lo), "+v"(c.hi));
             j.role = k == 0 ? ROLE_DRAFT1 : k == 1 ? ROLE_DRAFT2 : ROLE_VERIFY;
             j.z = (k == 0 ? a.z1 : k == 1 ? a.z2 : a.zR) + (size_t)i * a.zstride;
