@@ -11,7 +11,7 @@ group or alone, so:
   state the grouped decode step produced, is bit-identical to the readout of
   the same prefix at the same depth computed alone (teacher-forced on the
   vanilla schedule, one row per pass), for committed prefixes of 4 and of
-  18 chunks, on the 16-row and the 64-row GEMM paths;
+  18 chunks, on the GEMM paths of up to 16 and of 17 to 64 rows;
 * greedy LoopSpec stays bit-identical to vanilla decoding.
 The element-wise comparison of such branches with the fp64 oracle is in
 test_gpu_debug (its shared-prefix cases)."""
