@@ -49,7 +49,7 @@ PEAK_HBM_GBS = 8000.0
 # M = 2 rows at position 512): rocprofv3 FETCH_SIZE + WRITE_SIZE, each scaled
 # by what the counter reads for a plain 1 GiB copy.  Valid only for the
 # kernel sources it was measured on (their SHA-1 below); otherwise null.
-PASS_TRAFFIC = {"sources_sha1": "02cc1a7fb496612378535a71f55245968be0841a", "model": "ouro14", "M": 2,
+PASS_TRAFFIC = {"sources_sha1": "4966556264f29bf86f09a920e47f82e2c42a7b4f", "model": "ouro14", "M": 2,
                 "pos": 512, "bytes": 2697399992}
 PASS_SOURCES = ["ls_common.h", "ls_gemm.h", "ls_gemm_dev.h", "ls_attn.h", "ls_attn_dev.h", "ls_pass.h",
                 "ls_pass.hip"]
@@ -58,7 +58,7 @@ PASS_SOURCES = ["ls_common.h", "ls_gemm.h", "ls_gemm_dev.h", "ls_attn.h", "ls_at
 # HBM bytes of one core-block gate/up launch of the Raven-shaped model at
 # M = 2 rows (bench.py --counters: FETCH_SIZE + WRITE_SIZE per dispatch,
 # scaled like PASS_TRAFFIC); valid only for the GEMM sources it was measured on
-GU_TRAFFIC = {"sources_sha1": "67200fced04f77d1a5011a4bdc146e4f6e08063d", "model": "raven", "M": 2,
+GU_TRAFFIC = {"sources_sha1": "786af77bda6daf285e39c962a27c4ecacfdee245", "model": "raven", "M": 2,
               "bytes": 379813604}
 GEMM_SOURCES = ["ls_common.h", "ls_gemm.h", "ls_gemm_dev.h", "ls_gemm_sk.hip"]
 

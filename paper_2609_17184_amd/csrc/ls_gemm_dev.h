@@ -497,9 +497,10 @@ __device__ __forceinline__ void gemm_finish(const GemmParams& p, int item, int M
     } else {
         // Fragments not yet written by their producers are read again, all of
         // them in the same round (one round trip per round).  The sentinel is a
-        // NaN and a product with a NaN is one, so once every fragment's first
-        // word has arrived the products themselves are the test of the others:
-        // sums without a NaN used no sentinel.  Only sums with one (data late
+        // NaN and a product with a NaN is one (checked at every place of either
+        // type's operand, against zeros and infinities too), so once every
+        // fragment's first word has arrived the products themselves are the
+        // test of the others: sums without a NaN used no sentinel.  Only sums with one (data late
         // in part, or NaN or infinities among it) take the test of every word,
         // which cost 1.2 % of an Ouro-1.4B decode in front of the products.
         auto again = [&](const bool (&miss)[MAXS]) __attribute__((always_inline)) {
